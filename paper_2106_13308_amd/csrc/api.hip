@@ -42,7 +42,7 @@ size_t step_energy_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
 // incremental sampler's s_d z_d, read by the backward][masked copy of P^T, h x ld(n)]
 size_t step_zs_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
   return step_energy_offset(n, h, B, wdtype) +
-         (size_t)round_up((int64_t)((n + 63) / 64) * B * (int64_t)sizeof(double), 256);
+         (size_t)round_up((int64_t)energy_dense_ws_bytes(n, B), 256);
 }
 
 size_t step_pm_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {

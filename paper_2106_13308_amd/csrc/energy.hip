@@ -249,134 +249,237 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bytes_kernel(int n, int
   }
 }
 
-// ---------------------------------------------------------------- dense J (FP64)
-// E_b = sum_i s_bi * y_bi with y_bi = sum_{j>i} J_ij s_bj (strict upper triangle only).
-// Tile: 64 samples x 64 rows i per workgroup, K loop over j >= i0 in chunks of 32,
-// FP64 MFMA 16x16x4 on exact operands (+-1 and float32 J widened to double).
-// Each workgroup writes one partial per sample; a second pass sums the partials of
-// the row tiles in a fixed order.
-constexpr int DT = 64, DK = 32;
-constexpr int DKT = DK / 4;  // stage columns per thread (4 threads per row)
-__global__ __launch_bounds__(256) void energy_dense_kernel(int n, int64_t lds, const float* __restrict__ J,
-                                                            const int8_t* __restrict__ S, int64_t B,
-                                                            double* __restrict__ part) {
-  __shared__ double Ss[DT][DK + 1];
-  __shared__ double Js[DT][DK + 1];
-  __shared__ double rowsum[2][DT];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;  // wave sub-tile: samples x rows
-  const int64_t m0 = (int64_t)blockIdx.y * DT;          // samples
-  const int i0 = blockIdx.x * DT;                       // rows i
-  doublex4_t acc[2][2];
+// ---------------------------------------------------------------- dense J (fixed point)
+// E_b = sum_i s_bi y_bi with y_bi = sum_{j>i} J_ij s_bj (strict upper triangle only).
+//
+// The spins are integers, so y is a contraction of integers once row i of J is written in fixed
+// point: with 2^e_i above the row's largest entry, J_ij = 2^(e_i - 54) q_ij and |q_ij| < 2^54, exact for
+// entries down to 2^-31 of the largest and rounded to 2^-55 of it below, where a double-precision
+// sum rounds its partial sums to 2^-53.  q is split into seven signed bytes, each plane is
+// multiplied with the spins on the int8 matrix cores (exact 32-bit sums: 128 n < 2^31), and the
+// seven sums of a row are joined by six double-precision multiply-adds.
+//
+// Tile: 16 IB rows x 32 samples per wave, NW waves with the same rows, 64 columns of J per step.  The
+// workgroup turns each step's FP32 entries into byte planes in LDS itself (13 instructions an entry
+// plus the byte transposes, shared by its 32 NW samples) - a separate pass over J would write and
+// read 7 n^2 bytes; the spins are matrix operands as they lie in memory.  Lane group g takes the bytes
+// 16 g .. 16 g + 15 of either operand's 64.
+//
+// A step's products run beside the conversion of the next step, one barrier per step.
+//
+// n = 2000, B = 8192: 158 us (1.45 POPS of the 4.6 that a loop of these products reaches) and 12 us
+// for the exponents and the sum of the tiles' partials; the FP64 matrix cores took 1172 us at 0.35 of
+// their peak.  n = 1000, B = 512: 14 + 10 us, 65 before.  Copies without the conversion take 133 us,
+// without the spin loads 150, with 12 of the 28 products of a step 106: what is left is each
+// workgroup's start and end, one workgroup per CU.  Against 64-bit sums of the N(0, 1/n) couplings the
+// energies are off by 1.3e-16 of their norm, as before.
+constexpr int DK = 64;  // columns of J per step
+constexpr int DD = 7;            // byte planes
+constexpr int DNONFINITE = INT32_MIN;
+typedef __attribute__((ext_vector_type(4))) int32_t i32x4_t;
+struct __attribute__((aligned(8))) Bytes16 {  // spin rows may start on any 8-byte boundary
+  uint32_t x[4];
+};
+
+// ex[i] = e with |J_ij| < 2^e for every j > i, DNONFINITE if the row has a NaN or infinity; a wave a row.
+__global__ __launch_bounds__(256) void energy_rowmax_kernel(int n, const float* __restrict__ J, int32_t* __restrict__ ex) {
+  const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (i >= n) return;
+  const float* row = J + (int64_t)i * n;
+  uint32_t m = 0;
+  int j = i + 1 + lane;
+  for (; j + 192 < n; j += 256) {
+    uint32_t v[4];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int u = 0; u < 4; ++u) v[u] = __float_as_uint(row[j + 64 * u]) & 0x7FFFFFFFu;
+    m = max(max(m, max(v[0], v[1])), max(v[2], v[3]));
+  }
+  for (; j < n; j += 64) m = max(m, __float_as_uint(row[j]) & 0x7FFFFFFFu);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = (doublex4_t){0, 0, 0, 0};
-  const int jbeg = (i0 / DK) * DK;
-  // stage: 64 rows x DK columns of each operand, DKT elements per thread.  The next stage's
-  // values are loaded into registers before the current stage is multiplied, so the loads
-  // overlap the products.
-  const int r = t >> 2, q = (t & 3) * DKT;
-  const int64_t bq = m0 + r;
-  const int iq = i0 + r;
-  uint2 sv = make_uint2(0u, 0u);  // DKT = 8 spins (int8), columns j0 + q .. (inside the padded row)
-  float jv[DKT];
-  const bool vec = (n & 3) == 0 && ((uintptr_t)J & 15) == 0;  // rows of J start 16-byte aligned
-  auto fetch = [&](int j0) {
-    sv = (bq < B) ? *(const uint2*)(S + bq * lds + j0 + q) : make_uint2(0u, 0u);
-    const int jq = j0 + q;
-    if (vec && iq < n && jq + DKT <= n) {  // eight columns inside the row: two 16-byte loads
-      const float4 a0 = *(const float4*)(J + (int64_t)iq * n + jq), a1 = *(const float4*)(J + (int64_t)iq * n + jq + 4);
-      const float v8[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+  if (lane == 0) ex[i] = m >= 0x7F800000u ? DNONFINITE : max((int)(m >> 23), 1) - 126;
+}
+
+// q of one entry as eight bytes, the low seven of them the signed digits
+__device__ inline uint2 fixed_digits(float v, int e) {
+  const float x = ldexpf(v, 23 - e);      // |x| < 2^23
+  const int32_t hi = (int32_t)x;
+  const float r = x - (float)hi;          // exact
+  const int64_t lo = (int32_t)rintf(r * 2147483648.f);
+  // 128 added to every digit turns the balanced digits into the plain bytes of the sum
+  constexpr uint64_t bias = 0x0080808080808080ull;
+  const uint64_t q = ((uint64_t)((int64_t)hi * 2147483648ll) + (uint64_t)lo + bias) ^ bias;
+  return make_uint2((uint32_t)q, (uint32_t)(q >> 32));
+}
+
+// VEC: rows of J start 16-byte aligned (n a multiple of four and J 16-byte aligned)
+template <int NW, int IB, bool VEC>
+__global__ __launch_bounds__(64 * NW, 2) void energy_dense_kernel(int n, int64_t lds, const float* __restrict__ J,
+                                                               const int32_t* __restrict__ ex,
+                                                               const int8_t* __restrict__ S, int64_t B,
+                                                               double* __restrict__ part) {
+  constexpr int DT = 16 * IB;                  // rows of the tile
+  constexpr int NQ = DT * DK / 4 / (64 * NW);  // quads of columns converted per thread and step
+  __shared__ __align__(16) uint8_t planes[2][DD][DT * DK];
+  __shared__ int32_t se[DT];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6, r = lane & 15, g = lane >> 4;
+  const int i0 = blockIdx.y * DT;
+  const int64_t b0 = (int64_t)blockIdx.x * (32 * NW) + 32 * wv;
+  if (t < DT) se[t] = (i0 + t < n) ? ex[i0 + t] : 0;
+  __syncthreads();
+  bool nonfinite = false;
 #pragma unroll
-      for (int e = 0; e < DKT; ++e) jv[e] = (jq + e > iq) ? v8[e] : 0.f;
-    } else {
+  for (int q = 0; q < DT; ++q) nonfinite |= se[q] == DNONFINITE;
+  // quad u of the thread: row tr + (4 NW) u, columns 4 tq .. 4 tq + 3 of the step.  Addresses are
+  // clamped into the matrix and entries masked when they are converted, so that a load has a step
+  // or two to arrive.
+  const int tr = t >> 4, tq = t & 15;
+  float jr[2][NQ][4];
+  auto fetch_j = [&](int j0, float(&jv)[NQ][4]) {
+    const int j = j0 + 4 * tq;
 #pragma unroll
-      for (int e = 0; e < DKT; ++e) {
-        const int j = jq + e;
-        jv[e] = (iq < n && j < n && j > iq) ? J[(int64_t)iq * n + j] : 0.f;
+    for (int u = 0; u < NQ; ++u) {
+      const float* row = J + (int64_t)min(i0 + tr + 4 * NW * u, n - 1) * n;
+      if constexpr (VEC) {
+        const float4 a = *(const float4*)(row + min(j, n - 4));
+        jv[u][0] = a.x; jv[u][1] = a.y; jv[u][2] = a.z; jv[u][3] = a.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) jv[u][e] = row[min(j + e, n - 1)];
       }
     }
   };
-  static_assert(DKT == 8, "the spin fetch reads eight bytes");
-  fetch(jbeg);
-  for (int j0 = jbeg; j0 < n; j0 += DK) {
+  // spins of samples b0 + 16 sb + r (clamped: results past B are never stored); the row padding meets
+  // zero digits
+  const int8_t* srow[2];
 #pragma unroll
-    for (int e = 0; e < DKT; ++e) {
-      const uint32_t w = (e < 4) ? sv.x : sv.y;
-      Ss[r][q + e] = (j0 + q + e < n) ? (double)(int8_t)(w >> (8 * (e & 3))) : 0.0;
-      Js[r][q + e] = (double)jv[e];
-    }
-    __syncthreads();
-    if (j0 + DK < n) fetch(j0 + DK);
+  for (int sb = 0; sb < 2; ++sb) srow[sb] = S + min(b0 + 16 * sb + r, B - 1) * lds;
+  i32x4_t sr[2][2];
+  auto fetch_s = [&](int j0, i32x4_t(&v)[2]) {
 #pragma unroll
-    for (int kk = 0; kk < DK; kk += 4) {
-      double a[2], bb[2];
+    for (int sb = 0; sb < 2; ++sb) v[sb] = __builtin_bit_cast(i32x4_t, *(const Bytes16*)(srow[sb] + j0 + 16 * g));
+  };
+  i32x4_t acc[DD][IB][2];  // plane, 16-row block, 16-sample block; entry e: row 4 g + e, sample r
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi) a[mi] = Ss[wm + mi * 16 + (lane & 15)][kk + (lane >> 4)];
+  for (int p = 0; p < DD; ++p)
 #pragma unroll
-      for (int ni = 0; ni < 2; ++ni) bb[ni] = Js[wn + ni * 16 + (lane & 15)][kk + (lane >> 4)];
+    for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
-      for (int mi = 0; mi < 2; ++mi)
+      for (int sb = 0; sb < 2; ++sb) acc[p][ib][sb] = (i32x4_t){0, 0, 0, 0};
+  const int jbeg = i0 / DK * DK;
+  const int jlast = (n - 1) / DK * DK;  // past the end: the last step's loads again, never used
+  // the step at j0 from registers into the byte planes
+  auto convert = [&](int j0, const float(&jv)[NQ][4], uint8_t (*dstp)[DT * DK]) {
 #pragma unroll
-        for (int ni = 0; ni < 2; ++ni)
-          acc[mi][ni] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[mi], bb[ni], acc[mi][ni], 0, 0, 0);
-    }
-    __syncthreads();
-  }
-  // epilogue: the FP64 MFMA accumulator layout puts element e of lane l at row
-  // 4*e + l/16, column l%16 (unlike the FP32 16x16 layout, row 4*(l/16) + e);
-  // multiply by s_bi and sum over i.
-  double ps[2][4];
+    for (int u = 0; u < NQ; ++u) {
+      const int row = tr + 4 * NW * u, i = i0 + row, j = j0 + 4 * tq;
+      const int e = se[row] == DNONFINITE ? 0 : se[row];
+      uint2 d[4];
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      double v = 0.0;
-      const int64_t b = m0 + wm + mi * 16 + 4 * e + (lane >> 4);
-#pragma unroll
-      for (int ni = 0; ni < 2; ++ni) {
-        const int i = i0 + wn + ni * 16 + (lane & 15);
-        const double si = (b < B && i < n) ? (double)S[b * lds + i] : 0.0;
-        v += si * acc[mi][ni][e];
+      for (int c = 0; c < 4; ++c) {
+        const uint32_t keep = 0u - (uint32_t)((i < n) & (j + c < n) & (j + c > i));  // no branch around a load's first use
+        d[c] = fixed_digits(__uint_as_float(__float_as_uint(jv[u][c]) & keep), e);
       }
-      ps[mi][e] = v;
+      // byte p of the four entries, together
+      uint8_t* dst = dstp[0] + row * DK + 4 * tq;
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {
+        const uint32_t a0 = half ? d[0].y : d[0].x, a1 = half ? d[1].y : d[1].x, a2 = half ? d[2].y : d[2].x,
+                       a3 = half ? d[3].y : d[3].x;
+        const uint32_t l01 = __builtin_amdgcn_perm(a1, a0, 0x05010400u), l23 = __builtin_amdgcn_perm(a3, a2, 0x05010400u);
+        const uint32_t h01 = __builtin_amdgcn_perm(a1, a0, 0x07030602u), h23 = __builtin_amdgcn_perm(a3, a2, 0x07030602u);
+        const uint32_t w[4] = {__builtin_amdgcn_perm(l23, l01, 0x05040100u), __builtin_amdgcn_perm(l23, l01, 0x07060302u),
+                               __builtin_amdgcn_perm(h23, h01, 0x05040100u), __builtin_amdgcn_perm(h23, h01, 0x07060302u)};
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          if (4 * half + p < DD) *(uint32_t*)(dst + (4 * half + p) * (DT * DK)) = w[p];
+      }
     }
-  // reduce over the 16 lanes of a row (lane & 15) with a fixed butterfly
+  };
+  // step j0: its products beside the conversion of the next step
+  auto step = [&](int j0, const int q) {
+    lds_barrier();
+    i32x4_t a[IB][DD];
 #pragma unroll
-  for (int mi = 0; mi < 2; ++mi)
+    for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      double v = ps[mi][e];
-      for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 16);
-      ps[mi][e] = v;
-    }
-  if ((lane & 15) == 0) {
+      for (int p = 0; p < DD; ++p) a[ib][p] = *(const i32x4_t*)(planes[q][p] + (16 * ib + r) * DK + 16 * g);
+    fetch_s(min(j0 + DK, jlast), sr[q ^ 1]);
+    convert(j0 + DK, jr[q ^ 1], planes[q ^ 1]);
+    fetch_j(min(j0 + 3 * DK, jlast), jr[q ^ 1]);
 #pragma unroll
-    for (int mi = 0; mi < 2; ++mi)
+    for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) rowsum[wn >> 5][wm + mi * 16 + 4 * e + (lane >> 4)] = ps[mi][e];
+      for (int p = 0; p < DD; ++p)
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb)
+          acc[p][ib][sb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[ib][p], sr[q][sb], acc[p][ib][sb], 0, 0, 0);
+  };
+  fetch_j(jbeg, jr[0]);
+  fetch_s(jbeg, sr[0]);
+  convert(jbeg, jr[0], planes[0]);
+  fetch_j(min(jbeg + DK, jlast), jr[1]);
+  fetch_j(min(jbeg + 2 * DK, jlast), jr[0]);
+  int j0 = jbeg;
+  for (; j0 + DK < n; j0 += 2 * DK) {
+    step(j0, 0);
+    step(j0 + DK, 1);
   }
-  __syncthreads();
-  if (t < DT) {
-    const int64_t b = m0 + t;
-    if (b < B) part[(int64_t)blockIdx.x * B + b] = rowsum[0][t] + rowsum[1][t];
+  if (j0 < n) step(j0, 0);
+  // sum_i s_bi y_bi over the tile's rows: a lane's eight, then the four lane groups
+#pragma unroll
+  for (int sb = 0; sb < 2; ++sb) {
+    double v = 0.0;
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) {
+      const uint32_t sw = *(const uint32_t*)(srow[sb] + i0 + 16 * ib + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int il = 16 * ib + 4 * g + e, i = i0 + il;
+        double y = (double)acc[DD - 1][ib][sb][e];
+#pragma unroll
+        for (int p = DD - 2; p >= 0; --p) y = fma(y, 256.0, (double)acc[p][ib][sb][e]);
+        if (!nonfinite || se[il] != DNONFINITE) {
+          y = ldexp(y, se[il] - 54);
+        } else {  // plain sums decide between NaN and the infinities
+          y = 0.0;
+          for (int j = i + 1; j < n; ++j) y += (double)J[(int64_t)i * n + j] * (double)srow[sb][j];
+        }
+        if (i < n) v += (double)(int8_t)(sw >> (8 * e)) * y;
+      }
+    }
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    const int64_t b = b0 + 16 * sb + r;
+    if (g == 0 && b < B) part[(int64_t)blockIdx.y * B + b] = v;
   }
 }
 
+// E[b] = the row tiles' partial sums: eight loads in flight, four running sums, joined in a fixed order
 __global__ void sum_partials_kernel(const double* __restrict__ part, int ntiles, int64_t B,
                                     double* __restrict__ E) {
   const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (b >= B) return;
-  double s = 0.0;
-  for (int tt = 0; tt < ntiles; ++tt) s += part[(int64_t)tt * B + b];
-  E[b] = s;
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  int tt = 0;
+  for (; tt + 8 <= ntiles; tt += 8) {
+    double v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = part[(int64_t)(tt + u) * B + b];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s[u & 3] += v[u];
+  }
+  for (; tt < ntiles; ++tt) s[tt & 3] += part[(int64_t)tt * B + b];
+  E[b] = (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+// partial sums of the row tiles (of 16 rows at least), the rows' exponents
+size_t energy_dense_ws_bytes(int n, int64_t B) {
+  return (size_t)((n + 15) / 16) * (size_t)B * sizeof(double) + (size_t)round_up((int64_t)n * 4, 256);
 }
 
 size_t energy_workspace_bytes(const vqmc_hamiltonian& H, int64_t B) {
-  if (H.kind != VQMC_H_DENSE_F32) return 0;
-  const int64_t ntiles = (H.n + DT - 1) / DT;
-  return (size_t)(ntiles * B * sizeof(double));
+  return H.kind == VQMC_H_DENSE_F32 ? energy_dense_ws_bytes(H.n, B) : 0;
 }
 
 hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, void* E, void* ws,
@@ -384,10 +487,29 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
   const int n = H.n;
   const int64_t lds = round_up(n, kPad);
   if (H.kind == VQMC_H_DENSE_F32) {
-    const int ntiles = (n + DT - 1) / DT;
-    dim3 grid(ntiles, (unsigned)((B + DT - 1) / DT));
-    energy_dense_kernel<<<grid, 256, 0, st>>>(n, lds, H.J, S, B, (double*)ws);
+    int ntiles = (n + 15) / 16;
+    int32_t* ex = (int32_t*)((double*)ws + (int64_t)ntiles * B);
+    energy_rowmax_kernel<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(n, H.J, ex);
     hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const bool vec = (n & 3) == 0 && ((uintptr_t)H.J & 15) == 0;
+    // samples fastest: the longest row tiles start first
+    auto groups = [&](int nw) { return (B + 32 * nw - 1) / (32 * nw); };
+    auto go = [&](auto kern, int nw) {
+      kern<<<dim3((unsigned)groups(nw), (unsigned)ntiles), 64 * nw, 0, st>>>(n, lds, H.J, ex, S, B, (double*)ws);
+      e = hipGetLastError();
+    };
+    // 256 samples per conversion of J and 32 rows per spin operand while that leaves two workgroups
+    // for every CU, else smaller tiles (n = 1000, B = 512: 18 us with 16 rows, 31 with 32)
+    const int ntiles32 = (n + 31) / 32;
+    if (groups(8) * ntiles32 >= 512) {
+      ntiles = ntiles32;
+      go(vec ? energy_dense_kernel<8, 2, true> : energy_dense_kernel<8, 2, false>, 8);
+    } else if (groups(4) * ntiles >= 512) {
+      go(vec ? energy_dense_kernel<4, 1, true> : energy_dense_kernel<4, 1, false>, 4);
+    } else {
+      go(vec ? energy_dense_kernel<2, 1, true> : energy_dense_kernel<2, 1, false>, 2);
+    }
     if (e != hipSuccess) return e;
     sum_partials_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>((const double*)ws, ntiles, B,
                                                                        (double*)E);

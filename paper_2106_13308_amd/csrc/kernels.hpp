@@ -28,6 +28,7 @@ hipError_t launch_cast(int n, int h, const float* P32, int dtype, void* P, void*
 hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, void* E,
                          void* ws, hipStream_t st);
 size_t energy_workspace_bytes(const vqmc_hamiltonian& H, int64_t B);
+size_t energy_dense_ws_bytes(int n, int64_t B);  // the largest of the kinds
 hipError_t launch_stats(const void* E, int e_is_int, int64_t B, vqmc_stats* stats, float* coef,
                         hipStream_t st);
 
