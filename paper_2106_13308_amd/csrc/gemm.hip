@@ -19,9 +19,13 @@
 // [row][K] with K contiguous; the K step after next is loaded into registers while
 // the current one is multiplied, with two LDS buffers and one barrier per K step.  T = bf16
 // uses v_mfma_f32_16x16x32_bf16 (BK = 32); T = float uses v_mfma_f32_16x16x4_f32
-// (BK = 16).  Accumulation is always FP32.  Intermediates that a later product
+// (BK = 16; log p, its gradient and the SR factors in FP32 run in gemm_f32.hip instead: here are left
+// the plain sampler, whose draws, and the TIM forward pass, whose FP64 energies stay what they
+// are to the last bit, and the forward-mode product).  Accumulation is always FP32.  Intermediates that a later product
 // contracts over the batch (R, G, S, D) are written batch-contiguous (transposed) by
 // the producing epilogue, which the MFMA accumulator layout makes a 4-element store.
+#include <algorithm>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -664,7 +668,7 @@ __global__ __launch_bounds__(256) void grad_out_kernel(const float* __restrict__
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           *(uint4*)(go + 4 * v) = *(const uint4*)(gv + 4 * v);
-          *(uint4*)(so + 4 * v) = *(const uint4*)(svv + 4 * v);
+          if (St) *(uint4*)(so + 4 * v) = *(const uint4*)(svv + 4 * v);
         }
       }
     }
@@ -734,16 +738,17 @@ static WsLayout layout(int n, int h, int64_t B, int dtype, int which) {
     off += round_up((int64_t)bytes, 256);
     return o;
   };
-  L.R = take((size_t)B * g.ldh * es);
-  L.lp_part = take((size_t)g.nt_o * B * 4);
+  const int pf = dtype == VQMC_BF16 ? 1 : 2;  // FP32 tiles may have 32 rows or columns: twice the partial sums
+  L.R = take((size_t)std::max(B * g.ldh, h * g.ldB) * es);  // FP32 log p keeps it by unit
+  L.lp_part = take((size_t)pf * g.nt_o * B * 4);
   if (which == 1) {  // backward
     L.Rt = take((size_t)h * g.ldB * es);
     L.G = take((size_t)B * g.ldn * es);
     L.Gt = take((size_t)n * g.ldB * es);
     L.St = take((size_t)n * g.ldB * es);
-    L.Dt = take((size_t)h * g.ldB * es);
-    L.db2_part = take((size_t)g.mt_o * g.ldn * 4);
-    L.db1_part = take((size_t)g.mt_h * g.ldh * 4);
+    L.Dt = take((size_t)std::max(B * g.ldh, h * g.ldB) * es);  // the FP32 gradient keeps it by sample
+    L.db2_part = take((size_t)pf * g.mt_o * g.ldn * 4);
+    L.db1_part = take((size_t)pf * g.mt_h * g.ldh * 4);
   }
   if (which == 2) L.lp_acc = take((size_t)B * 4);  // plain sampler
   L.total = off;
@@ -763,16 +768,25 @@ static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   uint8_t* w = (uint8_t*)ws;
   T* R = (T*)(w + L.R);
   float* lp_part = (float*)(w + L.lp_part);
-  fwd_hidden_kernel<T, false><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1,
-                                                                     m.c, m.n, m.h, B, R, g.ldh, nullptr, g.ldB);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr,
-      nullptr, nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, g.nt_o, B, B, logp);
-  return hipGetLastError();
+  hipError_t e;
+  if constexpr (sizeof(T) == 4) {
+    int np = 0;
+    if ((e = launch_f32_hidden(m, S, B, nullptr, R, st)) != hipSuccess) return e;  // by unit, h x ld(B)
+    if ((e = launch_f32_logp(m, S, B, R, lp_part, Z, &np, st)) != hipSuccess) return e;
+    sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
+    return hipGetLastError();
+  } else {
+    fwd_hidden_kernel<T, false><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1,
+                                                                       m.c, m.n, m.h, B, R, g.ldh, nullptr, g.ldB);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
+        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr,
+        nullptr, nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, g.nt_o, B, B, logp);
+    return hipGetLastError();
+  }
 }
 
 template <typename T>
@@ -791,26 +805,36 @@ static hipError_t backward_t(const vqmc_made& m, const int8_t* S, int64_t B, con
   float* db2_part = (float*)(w + L.db2_part);
   float* db1_part = (float*)(w + L.db1_part);
   hipError_t e;
-  fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
-                                                                    m.n, m.h, B, R, g.ldh, Rt, g.ldB);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  // the first product does not read coef; it may overlap the work that produces it
-  if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
-  fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, coef, G, Gt,
-      St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
-                                                             g.ldB, db1_part, g.ldh);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  bwd_weight_kernel<T, false><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(Gt, Rt, g.ldB, m.c, m.n, m.h, dP);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  bwd_weight_kernel<T, true><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(St, Dt, g.ldB, m.c, m.n, m.h, dP);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  sum_rows_kernel<<<(unsigned)((m.n + 255) / 256), 256, 0, st>>>(db2_part, g.mt_o, g.ldn, m.n, db2);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  sum_rows_kernel<<<(unsigned)((m.h + 255) / 256), 256, 0, st>>>(db1_part, g.mt_h, g.ldh, m.h, db1);
-  return hipGetLastError();
+  if constexpr (sizeof(T) == 4) {
+    int np1 = 0, np2 = 0;
+    if ((e = launch_f32_hidden(m, S, B, R, Rt, st)) != hipSuccess) return e;
+    // the first product does not read coef; it may overlap the work that produces it
+    if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
+    if ((e = launch_f32_out_grad(m, S, B, Rt, coef, G, Gt, nullptr, db2_part, &np2, st)) != hipSuccess) return e;
+    if ((e = launch_f32_adjoint(m, B, Gt, Rt, Dt, nullptr, nullptr, db1_part, &np1, st)) != hipSuccess) return e;
+    return launch_f32_weight(m, S, B, G, R, Dt, dP, db2_part, np2, db1_part, np1, db2, db1, st);
+  } else {
+    fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
+                                                                      m.n, m.h, B, R, g.ldh, Rt, g.ldB);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // the first product does not read coef; it may overlap the work that produces it
+    if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
+    fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
+        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, coef, G, Gt,
+        St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
+                                                               g.ldB, db1_part, g.ldh);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    bwd_weight_kernel<T, false><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(Gt, Rt, g.ldB, m.c, m.n, m.h, dP);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    bwd_weight_kernel<T, true><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(St, Dt, g.ldB, m.c, m.n, m.h, dP);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    sum_rows_kernel<<<(unsigned)((m.n + 255) / 256), 256, 0, st>>>(db2_part, g.mt_o, g.ldn, m.n, db2);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    sum_rows_kernel<<<(unsigned)((m.h + 255) / 256), 256, 0, st>>>(db1_part, g.mt_h, g.ldh, m.h, db1);
+    return hipGetLastError();
+  }
 }
 
 // Factors of the per-sample scores for the SR Gram: the recompute path of backward_t with
@@ -827,18 +851,23 @@ size_t sr_gram_ws_bytes(int n, int h, int64_t B, int dtype) {
 // The hidden adjoint of the Gram's factors: BF16 with the sampler tables on the direct-to-LDS
 // engine (their masked copy of P^T), else the register-staged one.
 template <typename T>
-static hipError_t sr_hidden_adjoint(const vqmc_made& m, int64_t B, const Geom& g, const T* G, const T* Rt, T* Dt,
-                                    float* db1_part, hipStream_t st) {
-  if (sizeof(T) == 2 && m.band) {
-    int64_t zo, uo, po;
-    int nzt, nut;
-    sample_tables_layout(m.n, m.h, m.wdtype, &zo, &uo, &po, &nzt, &nut);
-    return launch_bwd_hidden2(m, B, (const uint16_t*)G, (const uint16_t*)((const uint8_t*)m.band + po),
-                              (const uint16_t*)Rt, (uint16_t*)Dt, db1_part, st);
+static hipError_t sr_hidden_adjoint(const vqmc_made& m, int64_t B, const Geom& g, const T* G, const T* Gt, const T* Rt,
+                                    T* Dt, float* db1_part, hipStream_t st) {
+  if constexpr (sizeof(T) == 4) {
+    int np1 = 0;
+    return launch_f32_adjoint(m, B, Gt, Rt, nullptr, Dt, nullptr, db1_part, &np1, st);
+  } else {
+    if (sizeof(T) == 2 && m.band) {
+      int64_t zo, uo, po;
+      int nzt, nut;
+      sample_tables_layout(m.n, m.h, m.wdtype, &zo, &uo, &po, &nzt, &nut);
+      return launch_bwd_hidden2(m, B, (const uint16_t*)G, (const uint16_t*)((const uint8_t*)m.band + po),
+                                (const uint16_t*)Rt, (uint16_t*)Dt, db1_part, st);
+    }
+    bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
+                                                               g.ldB, db1_part, g.ldh);
+    return hipGetLastError();
   }
-  bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
-                                                             g.ldB, db1_part, g.ldh);
-  return hipGetLastError();
 }
 
 template <typename T>
@@ -861,14 +890,20 @@ static hipError_t sr_gram_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   hipError_t e;
   fill_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(ones, B, 1.f);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
-                                                                    m.n, m.h, B, R, g.ldh, Rt, g.ldB);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, ones, G, Gt,
-      St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = sr_hidden_adjoint<T>(m, B, g, G, Rt, Dt, db1_part, st)) != hipSuccess) return e;
+  if constexpr (sizeof(T) == 4) {
+    int np2 = 0;
+    if ((e = launch_f32_hidden(m, S, B, nullptr, Rt, st)) != hipSuccess) return e;
+    if ((e = launch_f32_out_grad(m, S, B, Rt, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
+  } else {
+    fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
+                                                                      m.n, m.h, B, R, g.ldh, Rt, g.ldB);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
+        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, ones, G, Gt,
+        St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if ((e = sr_hidden_adjoint<T>(m, B, g, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   return launch_sr_gram_sweeps(m.wdtype, Gt, Rt, Dt, St, g.ldB, m.c, m.n, m.h, B, parts, K, st, G, S, g.ldn);
 }
 
@@ -895,7 +930,7 @@ static hipError_t sr_gram_sampled_t(const vqmc_made& m, const int8_t* S, int64_t
   if ((e = hipGetLastError()) != hipSuccess) return e;
   grad_out_kernel<T><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(Zs, S, g.ldn, ones, m.n, B, G, Gt, St, g.ldB, db2_part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = sr_hidden_adjoint<T>(m, B, g, G, Rt, Dt, db1_part, st)) != hipSuccess) return e;
+  if ((e = sr_hidden_adjoint<T>(m, B, g, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   return launch_sr_gram_sweeps(m.wdtype, Gt, Rt, Dt, St, g.ldB, m.c, m.n, m.h, B, parts, K, st, G, S, g.ldn);
 }
 
@@ -1012,7 +1047,9 @@ static hipError_t backward_sampled_t(const vqmc_made& m, const int8_t* S, int64_
   float* db2_part = (float*)(w + L.db2_part);
   float* db1_part = (float*)(w + L.db1_part);
   hipError_t e;
-  grad_out_kernel<T><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(Zs, S, g.ldn, coef, m.n, B, G, Gt, St, g.ldB, db2_part);
+  // (the FP32 weight gradient reads the spins by sample, as they are)
+  grad_out_kernel<T><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(Zs, S, g.ldn, coef, m.n, B, G, Gt,
+                                                           sizeof(T) == 2 ? St : nullptr, g.ldB, db2_part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if constexpr (sizeof(T) == 2) {
     // BF16: the direct-to-LDS engine, the adjoint's mask on a masked copy of P^T
@@ -1029,18 +1066,11 @@ static hipError_t backward_sampled_t(const vqmc_made& m, const int8_t* S, int64_
     return launch_backward_products2(m, B, G, Gt, St, Rt, Dt, (bf16_t*)Pm, db1_part, g.mt_h, db2_part, g.mt_o, dP,
                                      db1, db2, st, ready);
   } else {
-    bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
-                                                               g.ldB, db1_part, g.ldh);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    bwd_weight_kernel<T, false><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(Gt, Rt, g.ldB, m.c, m.n, m.h, dP);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    bwd_weight_kernel<T, true><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(St, Dt, g.ldB, m.c, m.n, m.h, dP);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    int np1 = 0;
+    T* R = (T*)(w + L.R);
+    if ((e = launch_f32_adjoint(m, B, Gt, Rt, Dt, nullptr, R, db1_part, &np1, st)) != hipSuccess) return e;
+    return launch_f32_weight(m, S, B, G, R, Dt, dP, db2_part, g.mt_o, db1_part, np1, db2, db1, st);
   }
-  sum_rows_kernel<<<(unsigned)((m.n + 255) / 256), 256, 0, st>>>(db2_part, g.mt_o, g.ldn, m.n, db2);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  sum_rows_kernel<<<(unsigned)((m.h + 255) / 256), 256, 0, st>>>(db1_part, g.mt_h, g.ldh, m.h, db1);
-  return hipGetLastError();
 }
 
 void* backward_rt_slot(const vqmc_made& m, int64_t B, void* ws) {
