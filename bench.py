@@ -219,18 +219,13 @@ def _dominant_desc(call, made, H):
         return {"kernels": ["energy_csr_bytes_kernel"], "src": ["energy.hip"], "bound": "hbm",
                 "peak": PEAK["hbm_gbs"], "unit": "GB/s", "metric": "gbs"}
     t = "bf16" if bf16 else "float"
-    if call == "backward_sampled" and bf16:
-        # with the sampler tables the masked copy of P^T is ready and the weight-gradient launch
-        # sums the bias partials, so these three are the call's launches
-        return {"kernels": ["grad_out_kernel<bf16>", "bwd_hidden2_kernel", "bwd_weight2_kernel"],
-                "src": ["gemm.hip", "gemm2.hip"], "bound": "mfma", "peak": mm, "unit": "TFLOP/s", "metric": "tflops"}
+    p, src = ("b", "gemm_bf16.hip") if bf16 else ("f32", "gemm_f32.hip")
+    products = [f"{p}_adjoint_kernel", f"{p}_weight_kernel"]  # the second sums the bias partials as well
     if call == "backward_sampled":
-        return {"kernels": [f"grad_out_kernel<{t}>", f"bwd_hidden_kernel<{t}>", f"bwd_weight_kernel<{t}, false>",
-                            f"bwd_weight_kernel<{t}, true>", "sum_rows_kernel"],
-                "src": ["gemm.hip"], "bound": "mfma", "peak": mm, "unit": "TFLOP/s", "metric": "tflops"}
-    return {"kernels": [f"fwd_hidden_kernel<{t}, true>", f"fwd_out_kernel<{t}, 1>", f"bwd_hidden_kernel<{t}>",
-                        f"bwd_weight_kernel<{t}, false>", f"bwd_weight_kernel<{t}, true>", "sum_rows_kernel"],
-            "src": ["gemm.hip"], "bound": "mfma", "peak": mm, "unit": "TFLOP/s", "metric": "tflops"}
+        return {"kernels": [f"grad_out_kernel<{t}>"] + products, "src": ["gemm.hip", src], "bound": "mfma", "peak": mm,
+                "unit": "TFLOP/s", "metric": "tflops"}
+    return {"kernels": [f"{p}_hidden_kernel", f"{p}_out_kernel"] + products, "src": [src], "bound": "mfma", "peak": mm,
+            "unit": "TFLOP/s", "metric": "tflops"}
 
 
 def _src_sha(files):

@@ -39,13 +39,13 @@ size_t step_energy_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
 }
 
 // Step workspace: [sampling / backward region][energy region][Zs: B x ld(n) floats, the
-// incremental sampler's s_d z_d, read by the backward][masked copy of P^T, h x ld(n)]
+// incremental sampler's s_d z_d, read by the backward]
 size_t step_zs_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
   return step_energy_offset(n, h, B, wdtype) +
          (size_t)round_up((int64_t)energy_dense_ws_bytes(n, B), 256);
 }
 
-size_t step_pm_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
+size_t step_ws_bytes(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
   return step_zs_offset(n, h, B, wdtype) + (size_t)round_up(B * round_up(n, kPad) * (int64_t)sizeof(float), 256);
 }
 
@@ -81,7 +81,7 @@ struct SrDirLayout {
   size_t K, solve, y, total;
 };
 SrDirLayout sr_dir_layout(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
-  const size_t bws = (size_t)round_up((int64_t)logprob_ws_bytes(n, h, B, wdtype, true), 256) + mask_w2t_bytes(n, h);
+  const size_t bws = logprob_ws_bytes(n, h, B, wdtype, true);
   const size_t r0 = (size_t)round_up((int64_t)std::max(sr_gram_ws_bytes(n, h, B, wdtype), bws), 256);
   SrDirLayout L;
   L.K = r0;
@@ -117,13 +117,9 @@ hipError_t noalloc_scratch(void** out) {
   return hipSuccess;
 }
 
-// TIM step workspace: [backward region (with the Rt slot)][masked copy of P^T][Zs: B x ld(n)
-// floats][TIM local-energy workspace]
-size_t tim_step_pm_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
-  return (size_t)round_up((int64_t)logprob_ws_bytes(n, h, B, wdtype, true), 256);
-}
+// TIM step workspace: [backward region (with the Rt slot)][Zs: B x ld(n) floats][TIM local-energy workspace]
 size_t tim_step_zs_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
-  return tim_step_pm_offset(n, h, B, wdtype) + (size_t)round_up((int64_t)mask_w2t_bytes(n, h), 256);
+  return (size_t)round_up((int64_t)logprob_ws_bytes(n, h, B, wdtype, true), 256);
 }
 size_t tim_step_tim_offset(int32_t n, int32_t h, int64_t B, int32_t wdtype) {
   return tim_step_zs_offset(n, h, B, wdtype) + (size_t)round_up(B * round_up(n, kPad) * (int64_t)sizeof(float), 256);
@@ -164,11 +160,10 @@ size_t vqmc_workspace_bytes(int which, int32_t n, int32_t h, int64_t B, int32_t 
     case VQMC_WS_LOGPROB: return logprob_ws_bytes(n, h, B, wdtype, false);
     case VQMC_WS_BACKWARD: return logprob_ws_bytes(n, h, B, wdtype, true);
     case VQMC_WS_SAMPLE_PLAIN: return sample_plain_ws_bytes(n, h, B, wdtype);
-    case VQMC_WS_STEP: return step_pm_offset(n, h, B, wdtype) + mask_w2t_bytes(n, h);
+    case VQMC_WS_STEP: return step_ws_bytes(n, h, B, wdtype);
     case VQMC_WS_SR_GRAM: return sr_gram_ws_bytes(n, h, B, wdtype);
     case VQMC_WS_SR_JVP: return sr_jvp_ws_bytes(n, h, B, wdtype);
-    case VQMC_WS_BACKWARD_SAMPLED:
-      return (size_t)round_up((int64_t)logprob_ws_bytes(n, h, B, wdtype, true), 256) + mask_w2t_bytes(n, h);
+    case VQMC_WS_BACKWARD_SAMPLED: return logprob_ws_bytes(n, h, B, wdtype, true);
     case VQMC_WS_SR_DIRECTION: return sr_dir_layout(n, h, B, wdtype).total;
     case VQMC_WS_TIM_ENERGY: return tim_ws_bytes(n, h, B, wdtype);
     case VQMC_WS_TIM_STEP: return tim_step_tim_offset(n, h, B, wdtype) + tim_ws_bytes(n, h, B, wdtype);
@@ -297,8 +292,7 @@ int vqmc_backward_sampled(const vqmc_made* m, const int8_t* S, int64_t B, const 
     return fail(VQMC_EINVAL, "bad backward arguments");
   const size_t need = vqmc_workspace_bytes(VQMC_WS_BACKWARD_SAMPLED, m->n, m->h, B, m->wdtype);
   if (ws_bytes < need) return fail(VQMC_EWORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
-  void* Pm = (uint8_t*)ws + round_up((int64_t)logprob_ws_bytes(m->n, m->h, B, m->wdtype, true), 256);
-  return hip_status(launch_backward_sampled(*m, S, B, coef, Zs, Rt, dP, db1, db2, ws, Pm, (hipStream_t)stream),
+  return hip_status(launch_backward_sampled(*m, S, B, coef, Zs, Rt, dP, db1, db2, ws, (hipStream_t)stream),
                     "vqmc_backward_sampled");
 }
 
@@ -457,8 +451,7 @@ int vqmc_sr_direction(const vqmc_made* m, const int8_t* S, int64_t B, const floa
   if ((e = launch_sr_solve(K, B, lambda * (double)B, coef, (double)B, y, w + L.solve, st)) != hipSuccess)
     return hip_status(e, "vqmc_sr_direction solve");
   if (Zs) {
-    void* Pm = w + round_up((int64_t)logprob_ws_bytes(m->n, m->h, B, m->wdtype, true), 256);
-    e = launch_backward_sampled(*m, S, B, y, Zs, Rt, xP, xb1, xb2, ws, Pm, st);
+    e = launch_backward_sampled(*m, S, B, y, Zs, Rt, xP, xb1, xb2, ws, st);
   } else {
     e = launch_backward(*m, S, B, y, xP, xb1, xb2, ws, st);
   }
@@ -497,8 +490,7 @@ int vqmc_step(const vqmc_made* m, const vqmc_hamiltonian* H, int64_t B, uint64_t
     if ((e = launch_energy(*H, S, B, E, ws_energy, st)) != hipSuccess) return hip_status(e, "vqmc_step energy");
     if ((e = launch_stats(E, H->kind == VQMC_H_CSR_INT, B, stats, coef, st)) != hipSuccess)
       return hip_status(e, "vqmc_step stats");
-    void* Pm = (uint8_t*)ws + step_pm_offset(m->n, m->h, B, m->wdtype);
-    if ((e = launch_backward_sampled(*m, S, B, coef, Zs, backward_rt_slot(*m, B, ws), dP, db1, db2, ws, Pm, st)) !=
+    if ((e = launch_backward_sampled(*m, S, B, coef, Zs, backward_rt_slot(*m, B, ws), dP, db1, db2, ws, st)) !=
         hipSuccess)
       return hip_status(e, "vqmc_step backward");
     return VQMC_OK;
@@ -564,8 +556,7 @@ int vqmc_tim_step(const vqmc_made* m, const vqmc_tim* H, int64_t B, uint64_t see
       hipSuccess)
     return hip_status(e, "vqmc_tim_step energy");
   if ((e = launch_stats(E, 0, B, stats, coef, st)) != hipSuccess) return hip_status(e, "vqmc_tim_step stats");
-  void* Pm = w + tim_step_pm_offset(m->n, m->h, B, m->wdtype);
-  if ((e = launch_backward_sampled(*m, S, B, coef, Zs, Rt, dP, db1, db2, ws, Pm, st)) != hipSuccess)
+  if ((e = launch_backward_sampled(*m, S, B, coef, Zs, Rt, dP, db1, db2, ws, st)) != hipSuccess)
     return hip_status(e, "vqmc_tim_step backward");
   return VQMC_OK;
 }

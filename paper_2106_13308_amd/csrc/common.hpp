@@ -99,6 +99,41 @@ __device__ inline void lds_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// ---------------------------------------------------------------- staircase masks
+// number of d in [0, n) with c[d] <= x (c non-decreasing), by a whole wave: 64 probes a time, so two
+// dependent loads up to n = 4096 where a bisection takes twelve
+__device__ inline int count_le_wave(const int32_t* __restrict__ c, int n, int x) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, len = n;
+  while (len > 0) {
+    const int step = (len + 63) / 64, at = lane * step;
+    const bool le = at < len && c[lo + min(at, len - 1)] <= x;
+    const int k = __popcll(__ballot(le));  // probes 0 .. k - 1 are <= x
+    if (k == 0) return lo;
+    const int end = min(k * step, len);
+    lo += (k - 1) * step + 1;
+    len = end - ((k - 1) * step + 1);
+  }
+  return lo;
+}
+
+// bound[u] = number of sites d with c[d] <= n0 + u (the units past h - 1: n), and the same count for
+// the tile's first and last unit.  Unit k receives the sites below its count and feeds the others.
+template <int BN, int NT>
+__device__ inline void unit_limits(int* bound, const int32_t* __restrict__ c, int n, int h, int n0, int& first, int& last) {
+  const int n1 = min(n0 + BN, h) - 1;
+  first = count_le_wave(c, n, n0);
+  last = count_le_wave(c, n, n1);
+  if (threadIdx.x < BN) bound[threadIdx.x] = n;
+  __syncthreads();
+  // the first site past unit u is the site d with c[d - 1] <= u < c[d]
+  for (int d = first + threadIdx.x; d <= min(last, n - 1); d += NT) {
+    const int u0 = max(d > 0 ? c[d - 1] : 0, n0), u1 = min(c[d] - 1, n1);
+    for (int u = u0; u <= u1; ++u) bound[u - n0] = d;
+  }
+  __syncthreads();
+}
+
 // sum_p part[p][i] over nparts rows of stride floats: the loads of eight parts are issued
 // together and summed in a fixed order (four running sums, then ((s0 + s1) + (s2 + s3))).
 __device__ inline float sum_parts(const float* __restrict__ part, int nparts, int64_t stride, int64_t i) {

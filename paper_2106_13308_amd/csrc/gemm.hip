@@ -19,11 +19,11 @@
 // [row][K] with K contiguous; the K step after next is loaded into registers while
 // the current one is multiplied, with two LDS buffers and one barrier per K step.  T = bf16
 // uses v_mfma_f32_16x16x32_bf16 (BK = 32); T = float uses v_mfma_f32_16x16x4_f32
-// (BK = 16; log p, its gradient and the SR factors in FP32 run in gemm_f32.hip instead: here are left
-// the plain sampler, whose draws, and the TIM forward pass, whose FP64 energies stay what they
-// are to the last bit, and the forward-mode product).  Accumulation is always FP32.  Intermediates that a later product
-// contracts over the batch (R, G, S, D) are written batch-contiguous (transposed) by
-// the producing epilogue, which the MFMA accumulator layout makes a 4-element store.
+// (BK = 16).  Accumulation is always FP32.  Intermediates that a later product contracts over the batch
+// (R, G, S, D) are written batch-contiguous (transposed) by the producing epilogue, which the MFMA
+// accumulator layout makes a 4-element store.  Log p, its gradient and the SR factors run in gemm_f32.hip
+// and gemm_bf16.hip instead: here are left the plain sampler and the FP32 TIM forward pass, whose draws and
+// FP64 energies stay what they are to the last bit, and the forward-mode product.
 #include <algorithm>
 
 #include "common.hpp"
@@ -262,11 +262,10 @@ __device__ inline RowsA<T, NV> rows_plain(const T* X, int64_t ld, int64_t R0, in
   return L;
 }
 
-// tile shapes of the four products
+// tile shapes of the products
 // 64 x 64 tiles everywhere: many workgroups per CU hide latency that one cannot
 constexpr int H_BM = 64, H_BN = 64;     // hidden-layer products (N = h)
 constexpr int O_BM = 64, O_BN = 64;     // output-layer product (N = n)
-constexpr int W_BM = 64, W_BN = 64;     // weight gradient (M = n, N = h)
 
 // ---------------------------------------------------------------- K1: first layer
 // A = S * P_upper + b1 ; writes R = relu(A) (B x ldh) and optionally Rt (h x ldB).
@@ -551,41 +550,6 @@ __global__ __launch_bounds__(256) void bwd_hidden_kernel(const T* __restrict__ G
   }
 }
 
-// ---------------------------------------------------------------- K4: weight gradient
-// UPPER = false: dP[d][k] = sum_b Gt[d][b] Rt[k][b] where k < c[d]   (dF/dW2)
-// UPPER = true:  dP[d][k] = sum_b St[d][b] Dt[k][b] where k >= c[d]  (dF/dW1)
-// Tiles without any element of their half return at once.
-template <typename T, bool UPPER>
-__global__ __launch_bounds__(256) void bwd_weight_kernel(const T* __restrict__ X, const T* __restrict__ Y,
-                                                          int64_t ldB, const int32_t* __restrict__ c,
-                                                          int n, int h, float* __restrict__ dP) {
-  using E = Engine<T, W_BM, W_BN>;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[E::SMEM];
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  const int wm = (wv >> 1) * (W_BM / 2), wn = (wv & 1) * (W_BN / 2);
-  const int r0 = t >> 2;
-  const int d0 = blockIdx.y * W_BM;   // sites
-  const int k0u = blockIdx.x * W_BN;  // units
-  const int dlast = min(d0 + W_BM - 1, n - 1);
-  const bool any = UPPER ? (k0u + W_BN - 1 >= c[d0]) : (k0u < c[dlast]);
-  if (!any) return;
-  const RowsA<T, E::AV> la = rows_plain<T, E::AV>(X, ldB, d0, n, (int)ldB, r0);
-  const RowsA<T, E::BV> lb = rows_plain<T, E::BV>(Y, ldB, k0u, h, (int)ldB, r0);
-  floatx4_t acc[E::FM][E::FN];
-  E::run(smem, 0, (int)ldB, la, lb, acc);
-#pragma unroll
-  for (int i = 0; i < E::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < E::FN; ++j) {
-      const int k = k0u + wn + j * 16 + (lane & 15);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int d = d0 + wm + i * 16 + 4 * (lane >> 4) + e;
-        if (d < n && k < h && (UPPER ? (k >= c[d]) : (k < c[d]))) dP[(int64_t)d * h + k] = acc[i][j][e];
-      }
-    }
-}
-
 // ---------------------------------------------------------------- K2': output adjoint from
 // the sampler's logits.  The incremental sampler has already evaluated every logit; with
 // zs = s_d z_d it gives G = coef_b s_d sigma(-zs) directly (G, and batch-contiguous Gt, St,
@@ -704,7 +668,6 @@ struct Geom {
   int64_t B, ldh, ldn, ldB;
   int mt_h, nt_h;   // hidden-layer grid: M tiles (batch) x N tiles (units)
   int mt_o, nt_o;   // output-layer grid: M tiles (batch) x N tiles (sites)
-  int mt_w, nt_w;   // weight-gradient grid: M tiles (sites) x N tiles (units)
 };
 
 static Geom geom(int n, int h, int64_t B) {
@@ -719,8 +682,6 @@ static Geom geom(int n, int h, int64_t B) {
   g.nt_h = (int)((g.ldh + H_BN - 1) / H_BN);
   g.mt_o = (int)((g.ldB + O_BM - 1) / O_BM);
   g.nt_o = (int)((g.ldn + O_BN - 1) / O_BN);
-  g.mt_w = (int)((g.ldn + W_BM - 1) / W_BM);
-  g.nt_w = (int)((g.ldh + W_BN - 1) / W_BN);
   return g;
 }
 
@@ -776,15 +737,10 @@ static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
     sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
     return hipGetLastError();
   } else {
-    fwd_hidden_kernel<T, false><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1,
-                                                                       m.c, m.n, m.h, B, R, g.ldh, nullptr, g.ldB);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr,
-        nullptr, nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, g.nt_o, B, B, logp);
+    int np = 0;
+    if ((e = launch_b_hidden(m, S, B, R, nullptr, nullptr, st)) != hipSuccess) return e;
+    if ((e = launch_b_logp(m, S, B, R, lp_part, Z, &np, st)) != hipSuccess) return e;
+    sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
     return hipGetLastError();
   }
 }
@@ -814,26 +770,13 @@ static hipError_t backward_t(const vqmc_made& m, const int8_t* S, int64_t B, con
     if ((e = launch_f32_adjoint(m, B, Gt, Rt, Dt, nullptr, nullptr, db1_part, &np1, st)) != hipSuccess) return e;
     return launch_f32_weight(m, S, B, G, R, Dt, dP, db2_part, np2, db1_part, np1, db2, db1, st);
   } else {
-    fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
-                                                                      m.n, m.h, B, R, g.ldh, Rt, g.ldB);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    int np1 = 0, np2 = 0;
+    if ((e = launch_b_hidden(m, S, B, R, Rt, nullptr, st)) != hipSuccess) return e;
     // the first product does not read coef; it may overlap the work that produces it
     if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
-    fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, coef, G, Gt,
-        St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
-                                                               g.ldB, db1_part, g.ldh);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    bwd_weight_kernel<T, false><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(Gt, Rt, g.ldB, m.c, m.n, m.h, dP);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    bwd_weight_kernel<T, true><<<dim3(g.nt_w, g.mt_w), 256, 0, st>>>(St, Dt, g.ldB, m.c, m.n, m.h, dP);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    sum_rows_kernel<<<(unsigned)((m.n + 255) / 256), 256, 0, st>>>(db2_part, g.mt_o, g.ldn, m.n, db2);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    sum_rows_kernel<<<(unsigned)((m.h + 255) / 256), 256, 0, st>>>(db1_part, g.mt_h, g.ldh, m.h, db1);
-    return hipGetLastError();
+    if ((e = launch_b_out_grad(m, S, B, R, coef, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
+    if ((e = launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st)) != hipSuccess) return e;
+    return launch_b_weight(m, B, Gt, St, Rt, Dt, dP, db2_part, np2, db1_part, np1, db2, db1, st);
   }
 }
 
@@ -848,26 +791,13 @@ size_t sr_gram_ws_bytes(int n, int h, int64_t B, int dtype) {
   return sr_extra_offset(n, h, B, dtype) + (size_t)round_up(B * 4, 256) + sr_gram_parts_bytes(n, h, B, dtype);
 }
 
-// The hidden adjoint of the Gram's factors: BF16 with the sampler tables on the direct-to-LDS
-// engine (their masked copy of P^T), else the register-staged one.
+// The hidden adjoint of the Gram's factors
 template <typename T>
-static hipError_t sr_hidden_adjoint(const vqmc_made& m, int64_t B, const Geom& g, const T* G, const T* Gt, const T* Rt,
-                                    T* Dt, float* db1_part, hipStream_t st) {
-  if constexpr (sizeof(T) == 4) {
-    int np1 = 0;
-    return launch_f32_adjoint(m, B, Gt, Rt, nullptr, Dt, nullptr, db1_part, &np1, st);
-  } else {
-    if (sizeof(T) == 2 && m.band) {
-      int64_t zo, uo, po;
-      int nzt, nut;
-      sample_tables_layout(m.n, m.h, m.wdtype, &zo, &uo, &po, &nzt, &nut);
-      return launch_bwd_hidden2(m, B, (const uint16_t*)G, (const uint16_t*)((const uint8_t*)m.band + po),
-                                (const uint16_t*)Rt, (uint16_t*)Dt, db1_part, st);
-    }
-    bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
-                                                               g.ldB, db1_part, g.ldh);
-    return hipGetLastError();
-  }
+static hipError_t sr_hidden_adjoint(const vqmc_made& m, int64_t B, const T* G, const T* Gt, const T* Rt, T* Dt,
+                                    float* db1_part, hipStream_t st) {
+  int np1 = 0;
+  if constexpr (sizeof(T) == 4) return launch_f32_adjoint(m, B, Gt, Rt, nullptr, Dt, nullptr, db1_part, &np1, st);
+  else return launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st);
 }
 
 template <typename T>
@@ -895,15 +825,11 @@ static hipError_t sr_gram_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
     if ((e = launch_f32_hidden(m, S, B, nullptr, Rt, st)) != hipSuccess) return e;
     if ((e = launch_f32_out_grad(m, S, B, Rt, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
   } else {
-    fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
-                                                                      m.n, m.h, B, R, g.ldh, Rt, g.ldB);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, ones, G, Gt,
-        St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    int np2 = 0;
+    if ((e = launch_b_hidden(m, S, B, R, Rt, nullptr, st)) != hipSuccess) return e;
+    if ((e = launch_b_out_grad(m, S, B, R, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
   }
-  if ((e = sr_hidden_adjoint<T>(m, B, g, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
+  if ((e = sr_hidden_adjoint<T>(m, B, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   return launch_sr_gram_sweeps(m.wdtype, Gt, Rt, Dt, St, g.ldB, m.c, m.n, m.h, B, parts, K, st, G, S, g.ldn);
 }
 
@@ -930,7 +856,7 @@ static hipError_t sr_gram_sampled_t(const vqmc_made& m, const int8_t* S, int64_t
   if ((e = hipGetLastError()) != hipSuccess) return e;
   grad_out_kernel<T><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(Zs, S, g.ldn, ones, m.n, B, G, Gt, St, g.ldB, db2_part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = sr_hidden_adjoint<T>(m, B, g, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
+  if ((e = sr_hidden_adjoint<T>(m, B, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   return launch_sr_gram_sweeps(m.wdtype, Gt, Rt, Dt, St, g.ldB, m.c, m.n, m.h, B, parts, K, st, G, S, g.ldn);
 }
 
@@ -1036,7 +962,7 @@ hipError_t launch_sr_jvp(const vqmc_made& m, const int8_t* S, int64_t B, const f
 template <typename T>
 static hipError_t backward_sampled_t(const vqmc_made& m, const int8_t* S, int64_t B, const float* coef,
                                      const float* Zs, const T* Rt, float* dP, float* db1, float* db2, void* ws,
-                                     void* Pm, hipStream_t st) {
+                                     hipStream_t st) {
   const Geom g = geom(m.n, m.h, B);
   const WsLayout L = layout(m.n, m.h, B, m.wdtype, 1);
   uint8_t* w = (uint8_t*)ws;
@@ -1052,19 +978,9 @@ static hipError_t backward_sampled_t(const vqmc_made& m, const int8_t* S, int64_
                                                            sizeof(T) == 2 ? St : nullptr, g.ldB, db2_part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if constexpr (sizeof(T) == 2) {
-    // BF16: the direct-to-LDS engine, the adjoint's mask on a masked copy of P^T
-    // the masked copy of P^T comes with the sampler tables when there are any
-    bool ready = false;
-    if (m.band) {
-      int64_t zo, uo, po;
-      int nzt, nut;
-      sample_tables_layout(m.n, m.h, m.wdtype, &zo, &uo, &po, &nzt, &nut);
-      Pm = (uint8_t*)m.band + po;
-      ready = true;
-    }
-    // (the weight-gradient launch also sums the bias-gradient partials)
-    return launch_backward_products2(m, B, G, Gt, St, Rt, Dt, (bf16_t*)Pm, db1_part, g.mt_h, db2_part, g.mt_o, dP,
-                                     db1, db2, st, ready);
+    int np1 = 0;
+    if ((e = launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st)) != hipSuccess) return e;
+    return launch_b_weight(m, B, Gt, St, Rt, Dt, dP, db2_part, g.mt_o, db1_part, np1, db2, db1, st);
   } else {
     int np1 = 0;
     T* R = (T*)(w + L.R);
@@ -1079,10 +995,10 @@ void* backward_rt_slot(const vqmc_made& m, int64_t B, void* ws) {
 
 hipError_t launch_backward_sampled(const vqmc_made& m, const int8_t* S, int64_t B, const float* coef,
                                    const float* Zs, const void* Rt, float* dP, float* db1, float* db2, void* ws,
-                                   void* Pm, hipStream_t st) {
+                                   hipStream_t st) {
   if (m.wdtype == VQMC_BF16)
-    return backward_sampled_t<bf16_t>(m, S, B, coef, Zs, (const bf16_t*)Rt, dP, db1, db2, ws, Pm, st);
-  return backward_sampled_t<float>(m, S, B, coef, Zs, (const float*)Rt, dP, db1, db2, ws, Pm, st);
+    return backward_sampled_t<bf16_t>(m, S, B, coef, Zs, (const bf16_t*)Rt, dP, db1, db2, ws, st);
+  return backward_sampled_t<float>(m, S, B, coef, Zs, (const float*)Rt, dP, db1, db2, ws, st);
 }
 
 template <typename T>
@@ -1125,17 +1041,23 @@ static hipError_t tim_forward_t(const vqmc_made& m, const int8_t* S, int64_t B, 
   uint8_t* w = (uint8_t*)ws;
   T* R = (T*)(w + L.R);
   float* lp_part = (float*)(w + L.lp_part);
-  fwd_hidden_kernel<T, false><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n,
-                                                                     m.h, B, R, g.ldh, nullptr, g.ldB);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr,
-      nullptr, nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  fwd_hidden_kernel<T, false, false, float><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(
-      S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n, m.h, B, A, g.ldh, (T*)nullptr, g.ldB);
-  return hipGetLastError();
+  if constexpr (sizeof(T) == 2) {
+    hipError_t e = launch_b_hidden(m, S, B, R, nullptr, A, st);
+    int np = 0;
+    return e != hipSuccess ? e : launch_b_logp(m, S, B, R, lp_part, Z, &np, st);
+  } else {
+    fwd_hidden_kernel<T, false><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n,
+                                                                       m.h, B, R, g.ldh, nullptr, g.ldB);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
+        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr,
+        nullptr, nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    fwd_hidden_kernel<T, false, false, float><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(
+        S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n, m.h, B, A, g.ldh, (T*)nullptr, g.ldB);
+    return hipGetLastError();
+  }
 }
 
 hipError_t launch_tim_forward(const vqmc_made& m, const int8_t* S, int64_t B, float* Z, float* A, void* ws,

@@ -43,7 +43,7 @@ struct F32 {
   static constexpr int NT = 64 * WM * WN * WK, BM = 32 * WM, BN = 32 * WN;
   static constexpr int NI = BM * BN / NT;  // tile elements per thread
   float red[WK][BM][BN + 1];
-  int bound[BN];  // limits of the tile's columns (f_limits)
+  int bound[BN];  // limits of the tile's columns (unit_limits)
 
   __device__ static int wave() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
   // first row and column of this wave's part of the tile
@@ -187,40 +187,6 @@ struct FSpinRows {
   }
 };
 
-// number of d in [0, n) with c[d] <= x (c non-decreasing), by a whole wave: 64 probes a time, so two
-// dependent loads up to n = 4096 where a bisection takes twelve
-__device__ inline int f_count_le(const int32_t* __restrict__ c, int n, int x) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, len = n;
-  while (len > 0) {
-    const int step = (len + 63) / 64, at = lane * step;
-    const bool le = at < len && c[lo + min(at, len - 1)] <= x;
-    const int k = __popcll(__ballot(le));  // probes 0 .. k - 1 are <= x
-    if (k == 0) return lo;
-    const int end = min(k * step, len);
-    lo += (k - 1) * step + 1;
-    len = end - ((k - 1) * step + 1);
-  }
-  return lo;
-}
-
-// e.bound[u] = number of sites d with c[d] <= n0 + u (the units past h - 1: n), and the same count for
-// the tile's first and last unit.  Unit k receives the sites below its count and feeds the others.
-template <class E>
-__device__ inline void f_limits(E& e, const int32_t* __restrict__ c, int n, int h, int n0, int& first, int& last) {
-  const int n1 = min(n0 + E::BN, h) - 1;
-  first = f_count_le(c, n, n0);
-  last = f_count_le(c, n, n1);
-  if (threadIdx.x < E::BN) e.bound[threadIdx.x] = n;
-  __syncthreads();
-  // the first site past unit u is the site d with c[d - 1] <= u < c[d]
-  for (int d = first + threadIdx.x; d <= min(last, n - 1); d += E::NT) {
-    const int u0 = max(d > 0 ? c[d - 1] : 0, n0), u1 = min(c[d] - 1, n1);
-    for (int u = u0; u <= u1; ++u) e.bound[u - n0] = d;
-  }
-  __syncthreads();
-}
-
 // Column tile of a workgroup.  The K ranges grow or shrink along the columns; workgroups are dealt
 // round-robin to the 8 XCDs and, in grids of one or two workgroups per CU, the second half lands on the
 // CUs of the first.  So each row of tiles starts one column further on, and the second half of the rows
@@ -242,7 +208,7 @@ __global__ __launch_bounds__(E::NT) void f32_hidden_kernel(const int8_t* __restr
   const int64_t m0 = (int64_t)blockIdx.y * E::BM;  // samples
   const int n0 = f_column() * E::BN;               // units
   int first, last;
-  f_limits(e, c, n, h, n0, first, last);
+  unit_limits<E::BN, E::NT>(e.bound, c, n, h, n0, first, last);
   const int kb = n0 + threadIdx.x % E::BN;  // the thread's unit in the epilogue
   const float bias = kb < h ? b1[kb] : 0.f;
   e.run(FSpinRows(S, lds, m0 + E::row0(), B),
@@ -347,7 +313,7 @@ __global__ __launch_bounds__(E::NT) void f32_adjoint_kernel(const float* __restr
   const int64_t m0 = (int64_t)blockIdx.y * E::BM;  // samples
   const int n0 = f_column() * E::BN;               // units
   int first, last;
-  f_limits(e, c, n, h, n0, first, last);
+  unit_limits<E::BN, E::NT>(e.bound, c, n, h, n0, first, last);
   // relu(A) of the thread's elements, loaded before the products
   const int t = threadIdx.x, m = t % E::BM;
   float rv[E::NI];

@@ -51,7 +51,6 @@ hipError_t launch_sample_pipe_cycles(const vqmc_made& m, int64_t B, uint64_t see
                                      float* logp, uint64_t* cycles, hipStream_t st);
 hipError_t launch_band(const vqmc_made& m, float* band, hipStream_t st, bool tiles = true);
 void sample_tables_layout(int n, int h, int wdtype, int64_t* z, int64_t* u, int64_t* pm, int* nzt, int* nut);
-hipError_t launch_mask_w2t(const vqmc_made& m, uint16_t* Pm, hipStream_t st);
 hipError_t launch_uniforms(int n, int64_t B, uint64_t seed, uint64_t step, int64_t offset, uint32_t tag,
                            float* u, hipStream_t st);
 
@@ -69,7 +68,7 @@ hipError_t launch_backward(const vqmc_made& m, const int8_t* S, int64_t B, const
 void* backward_rt_slot(const vqmc_made& m, int64_t B, void* ws);
 hipError_t launch_backward_sampled(const vqmc_made& m, const int8_t* S, int64_t B, const float* coef,
                                    const float* Zs, const void* Rt, float* dP, float* db1, float* db2, void* ws,
-                                   void* Pm, hipStream_t st);
+                                   hipStream_t st);
 // SR Gram (sr.hip): the factor rows come from the backward engine with coef = 1
 size_t sr_gram_ws_bytes(int n, int h, int64_t B, int dtype);
 hipError_t launch_sr_gram(const vqmc_made& m, const int8_t* S, int64_t B, float* K, void* ws, hipStream_t st);
@@ -105,16 +104,21 @@ hipError_t launch_f32_adjoint(const vqmc_made& m, int64_t B, const float* Gt, co
 hipError_t launch_f32_weight(const vqmc_made& m, const int8_t* S, int64_t B, const float* G, const float* R,
                              const float* D, float* dP, const float* db2_part, int np2, const float* db1_part, int np1,
                              float* db2, float* db1, hipStream_t st);
-// gemm2.hip: BF16 backward products on the direct-to-LDS engine; Pm: h x ld(n) bf16 scratch
-size_t mask_w2t_bytes(int n, int h);
-// the hidden adjoint alone: Dt = [Rt > 0] (G Pm^T)^T, db1 partials per 64-sample tile (ld(h) each)
-hipError_t launch_bwd_hidden2(const vqmc_made& m, int64_t B, const uint16_t* G, const uint16_t* Pm,
-                              const uint16_t* Rt, uint16_t* Dt, float* db1_part, hipStream_t st);
-// db1_part (np1 rows of ld(h)) and db2_part (np2 rows of ld(n)) are summed into db1 and db2
-hipError_t launch_backward_products2(const vqmc_made& m, int64_t B, const uint16_t* G, const uint16_t* Gt,
-                                     const uint16_t* St, const uint16_t* Rt, uint16_t* Dt, uint16_t* Pm,
-                                     float* db1_part, int np1, const float* db2_part, int np2, float* dP, float* db1,
-                                     float* db2, hipStream_t st, bool pm_ready);
+// gemm_bf16.hip: the BF16 products.  R: B x ld(h); Rt: h x ld(B); G: B x ld(n); Gt, St: n x ld(B); the number of
+// partial sums written (rows of B in lp_part, of ld(n) in db2_part, of ld(h) in db1_part) comes back in nparts, np2,
+// np1.
+hipError_t launch_b_hidden(const vqmc_made& m, const int8_t* S, int64_t B, uint16_t* R, uint16_t* Rt /* nullable */,
+                           float* A /* nullable: FP32 pre-activations, B x ld(h) */, hipStream_t st);
+hipError_t launch_b_logp(const vqmc_made& m, const int8_t* S, int64_t B, const uint16_t* R, float* lp_part,
+                         float* Z /* nullable */, int* nparts, hipStream_t st);
+hipError_t launch_b_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, const uint16_t* R, const float* coef,
+                             uint16_t* G, uint16_t* Gt, uint16_t* St, float* db2_part, int* np2, hipStream_t st);
+hipError_t launch_b_adjoint(const vqmc_made& m, int64_t B, const uint16_t* G, const uint16_t* Rt, uint16_t* Dt,
+                            float* db1_part, int* np1, hipStream_t st);
+// dP, and db1, db2 from their partial sums
+hipError_t launch_b_weight(const vqmc_made& m, int64_t B, const uint16_t* Gt, const uint16_t* St, const uint16_t* Rt,
+                           const uint16_t* Dt, float* dP, const float* db2_part, int np2, const float* db1_part, int np1,
+                           float* db2, float* db1, hipStream_t st);
 // TIM local energy (tim.hip): forward quantities (gemm.hip), then the single-flip differences
 hipError_t launch_tim_forward(const vqmc_made& m, const int8_t* S, int64_t B, float* Z, float* A, void* ws,
                               hipStream_t st);

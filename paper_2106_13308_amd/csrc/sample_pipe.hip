@@ -108,7 +108,7 @@ __host__ __device__ inline SpTables sp_tables(int n, int h, int wdtype) {
   t.z = round_up((int64_t)h * VQMC_BAND_REC * 4, 256);
   t.u = t.z + (int64_t)nb * t.nzt * t.zt;
   t.pm = round_up(t.u + (int64_t)nb * t.nut * t.ut, 256);
-  // BF16: then the backward's masked copy of P^T, h x ld(n) (unit k feeds site d: k < c[d])
+  // BF16: then the masked copy of P^T, h x ld(n) (unit k feeds site d: k < c[d])
   t.bytes = bf ? t.pm + (int64_t)h * round_up(n, 64) * 2 : t.pm;
   return t;
 }
@@ -895,6 +895,31 @@ __global__ __launch_bounds__(256) void utile_kernel(const WT* __restrict__ Pt, i
   }
 }
 
+// Masked copy of P^T: Pm[k][d] = P[d][k] where unit k feeds site d (k < c[d]), 0 elsewhere (and for d >= n)
+__global__ __launch_bounds__(256) void mask_w2t_kernel(const bf16_t* __restrict__ Pt, int64_t ldn,
+                                                        const int32_t* __restrict__ c, int n, int h,
+                                                        bf16_t* __restrict__ Pm) {
+  // block (x, k): row k, eight-element vectors 256x .. 256x + 255
+  const int k = blockIdx.y;
+  const int d0 = (blockIdx.x * 256 + threadIdx.x) * 8;
+  if (d0 >= ldn) return;
+  uint4 v = *(const uint4*)(Pt + (int64_t)k * ldn + d0);
+  int cd[8];
+  if (d0 + 8 <= n) {
+    const int4 c0 = *(const int4*)(c + d0), c1 = *(const int4*)(c + d0 + 4);
+    cd[0] = c0.x; cd[1] = c0.y; cd[2] = c0.z; cd[3] = c0.w;
+    cd[4] = c1.x; cd[5] = c1.y; cd[6] = c1.z; cd[7] = c1.w;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) cd[q] = (d0 + q < n) ? c[d0 + q] : 0;
+  }
+  bf16_t* e = (bf16_t*)&v;
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+    if (cd[q] <= k) e[q] = 0;  // also every site >= n (cd = 0)
+  *(uint4*)(Pm + (int64_t)k * ldn + d0) = v;
+}
+
 hipError_t launch_band(const vqmc_made& m, float* band, hipStream_t st, bool tiles) {
   const unsigned grid = (unsigned)((m.h + 3) / 4);
   const int64_t ldn = round_up(m.n, kPad);
@@ -914,7 +939,8 @@ hipError_t launch_band(const vqmc_made& m, float* band, hipStream_t st, bool til
     ztile_kernel<bf16_t><<<gz, 256, 0, st>>>((const bf16_t*)m.P, ldh, m.b2, m.n, nb, tb.nzt, tab + tb.z);
     utile_kernel<bf16_t><<<gu, 256, 0, st>>>((const bf16_t*)m.Pt, ldn, m.h, nb, tb.nut, tab + tb.u);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    e = launch_mask_w2t(m, (bf16_t*)(tab + tb.pm), st);
+    mask_w2t_kernel<<<dim3((unsigned)((ldn / 8 + 255) / 256), (unsigned)m.h), 256, 0, st>>>((const bf16_t*)m.Pt, ldn, m.c, m.n,
+                                                                                           m.h, (bf16_t*)(tab + tb.pm));
   } else {
     ztile_kernel<float><<<gz, 256, 0, st>>>((const float*)m.P, ldh, m.b2, m.n, nb, tb.nzt, tab + tb.z);
     utile_kernel<float><<<gu, 256, 0, st>>>((const float*)m.Pt, ldn, m.h, nb, tb.nut, tab + tb.u);
