@@ -7,8 +7,10 @@
 // so the only dense linear algebra is this B x B system.  It is solved in FP64 by a blocked
 // right-looking Cholesky factorisation L L^T = K + shift I (64 x 64 blocks, the matrix padded
 // to a multiple of 64 with identity rows) and a blocked back substitution L^T y = w.  The
-// right-hand side is one more row of the matrix (block row nb, its first row): the block-row
-// solve that makes L_ij out of A_ij turns it into w = L^-1 rhs.
+// right-hand side is one more row of the matrix (row ld; as block row nb every row of the block is that
+// one, and the first is stored): the block-row solve that makes L_ij out of A_ij turns it into
+// w = L^-1 rhs.  The factor of a diagonal block is kept right of it (chol_diag), above the diagonal,
+// where the matrix is not used.
 //
 // Launches, nb = padded B / 64 block columns:
 //   chol_init_kernel    the lower triangle of K + shift I in FP64, and the right-hand side;
@@ -30,20 +32,26 @@ constexpr int CL = CB + 2;   // LDS row stride (doubles): 16-byte aligned rows, 
 constexpr unsigned long long kUnknown = 0xFFF8C0DEC0DEC0DEull;
 
 // Lower triangle (by blocks) of K + shift I on the B x B part, identity on the padding; row ld is
-// scale * rhs, the rest of its block zero.
+// scale * rhs.
 __global__ void chol_init_kernel(const float* __restrict__ K, int64_t B, int64_t ld, double shift,
                                  const float* __restrict__ rhs, double scale, double* __restrict__ A,
                                  unsigned long long* __restrict__ y) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= ld * (ld + CB)) return;
+  if (idx >= ld * (ld + 1)) return;
   const int64_t r = idx / ld, c = idx - r * ld;
   if (r / CB < c / CB) return;
   double v;
-  if (r >= ld) v = (r == ld && c < B) ? scale * (double)rhs[c] : 0.0;
+  if (r == ld) v = c < B ? scale * (double)rhs[c] : 0.0;
   else if (r < B && c < B) v = (double)K[r * B + c] + (r == c ? shift : 0.0);
   else v = (r == c) ? 1.0 : 0.0;
   A[idx] = v;
   if (r == ld) y[c] = kUnknown;
+}
+
+// The factor of diagonal block i (row stride ld): in the block right of it, which nothing else uses; the
+// last one in place, where the one workgroup of its step has read the block already
+__device__ inline double* chol_diag(double* A, int64_t ld, int nb, int i) {
+  return A + (int64_t)i * CB * ld + (int64_t)min(i + 1, nb - 1) * CB;
 }
 
 // 1 / sqrt(d): the hardware estimate (about 24 bits) and one step of third order,
@@ -145,8 +153,7 @@ __device__ inline void chol_columns(double (&x)[CP], double (&y)[CP], double rs)
 // wave 0 beside the factor 0.95 ms; the panels' multipliers through v_readlane (8 - 10 cycles each)
 // 0.69 ms; the panel and tile loops unrolled (32 KB of code, fetched anew by every launch) 0.74 ms.
 constexpr int CW = 8;   // waves per workgroup
-__global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__ A, int64_t ld, int nb, int j,
-                                                            double* __restrict__ Ld) {
+__global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__ A, int64_t ld, int nb, int j) {
   __shared__ __align__(16) double D[CB][CL];               // diagonal block (j + 1, j + 1)
   __shared__ __align__(16) double Ls[CB][CL];              // L_j+1,j
   __shared__ __align__(16) double V[CB / CP][CP][CP + 2];  // L_pp^-1
@@ -167,14 +174,14 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
     // each wave sixteen rows, half of the columns
     const int64_t i0 = (int64_t)(j + 2 + q) * CB + 16 * (w & 3), k0 = (int64_t)(j + 2 + k) * CB + 32 * (w >> 2);
     double a[16], b0[16], b1[16], c0[4], c1[4];
-    chol_frag<16>(A + (i0 + r) * ld + jc + 4 * g, a);
+    chol_frag<16>(A + min(i0 + r, ld) * ld + jc + 4 * g, a);
     chol_frag<16>(A + (k0 + r) * ld + jc + 4 * g, b0);
     chol_frag<16>(A + (k0 + 16 + r) * ld + jc + 4 * g, b1);
-    double* c = A + (i0 + g) * ld + k0 + r;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      c0[e] = c[(int64_t)4 * e * ld];
-      c1[e] = c[(int64_t)4 * e * ld + 16];
+      const double* c = A + min(i0 + g + 4 * e, ld) * ld + k0 + r;
+      c0[e] = c[0];
+      c1[e] = c[16];
     }
     doublex4_t s0 = {0.0, 0.0, 0.0, 0.0}, s1 = s0;
 #pragma unroll
@@ -184,8 +191,10 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      c[(int64_t)4 * e * ld] = c0[e] - s0[e];
-      c[(int64_t)4 * e * ld + 16] = c1[e] - s1[e];
+      if (i0 + g + 4 * e > ld) continue;
+      double* c = A + (i0 + g + 4 * e) * ld + k0 + r;
+      c[0] = c0[e] - s0[e];
+      c[16] = c1[e] - s1[e];
     }
     return;
   }
@@ -196,13 +205,15 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
   const int pi = 4 * (r & 3) + (r >> 2);
   const bool owner = w == 1 || w > 4;
   const int ow = w == 1 ? 3 : (w - 5) & 3;  // rows 16 ow .. of the own block
-  double* own = A + (i0 + 16 * ow + r) * ld + d0 + 4 * g;
+  const int64_t orow = min(i0 + 16 * ow + r, ld);
+  const bool keep = orow == i0 + 16 * ow + r;  // not a copy of the right-hand side
+  double* own = A + orow * ld + d0 + 4 * g;
   doublex4_t o[4];  // tiles from the current panel's on
   double ob[16];
   // every load is issued before the first is waited for
   const int rq = t >> 5, cq = 2 * (t & 31);  // rows rq + 12 i, columns cq, cq + 1
   if (owner) {
-    if (j >= 0) chol_frag<16>(A + (i0 + 16 * ow + r) * ld + jc + 4 * g, ob);
+    if (j >= 0) chol_frag<16>(A + orow * ld + jc + 4 * g, ob);
 #pragma unroll
     for (int ct = 0; ct < 4; ++ct) {
       const double2 u = *(const double2*)(own + 16 * ct), v = *(const double2*)(own + 16 * ct + 2);
@@ -254,8 +265,10 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
     doublex4_t xp = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) xp = __builtin_amdgcn_mfma_f64_16x16x4f64(v[kk], o[0][kk], xp, 0, 0, 0);
-    *(double2*)(own + 16 * p) = make_double2(xp[0], xp[1]);
-    *(double2*)(own + 16 * p + 2) = make_double2(xp[2], xp[3]);
+    if (keep) {
+      *(double2*)(own + 16 * p) = make_double2(xp[0], xp[1]);
+      *(double2*)(own + 16 * p + 2) = make_double2(xp[2], xp[3]);
+    }
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
       o[u] = o[u + 1];
@@ -314,10 +327,10 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
   }
   if (w < 4 && (int)blockIdx.x == npanel - 1) {
     // the diagonal block's factor goes to its own place: other workgroups may still be reading the block
-    double* L = Ld + (int64_t)(j + 1) * CB * CB;
+    double* L = chol_diag(A, ld, nb, j + 1);
     for (int row = rq; row < CB; row += 8) {
       const double2 v = *(const double2*)&D[row][cq];
-      *(double2*)(L + row * CB + cq) = make_double2(cq <= row ? v.x : 0.0, cq + 1 <= row ? v.y : 0.0);
+      *(double2*)(L + row * ld + cq) = make_double2(cq <= row ? v.x : 0.0, cq + 1 <= row ? v.y : 0.0);
     }
   }
 }
@@ -331,8 +344,7 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
 // per block is one such hand-over and two 64 x 64 matrix-vector products: the inverse of L_ii is
 // formed before the first wait and the next L_ji is loaded before its y_j is awaited.
 constexpr int kSpin = 1 << 22;
-__global__ __launch_bounds__(256) void chol_back_kernel(const double* __restrict__ A, int64_t ld, int nb,
-                                                        const double* __restrict__ Ld, unsigned long long* y,
+__global__ __launch_bounds__(256) void chol_back_kernel(double* __restrict__ A, int64_t ld, int nb, unsigned long long* y,
                                                         int64_t B, float* __restrict__ out) {
   __shared__ __align__(16) double L[CB][CL];
   __shared__ __align__(16) double X[CB][CL];  // L_ii^-1
@@ -341,7 +353,8 @@ __global__ __launch_bounds__(256) void chol_back_kernel(const double* __restrict
   const int t = threadIdx.x, c = t & 63, q = t >> 6;
   const int i = nb - 1 - (int)blockIdx.x;
   const int64_t i0 = (int64_t)i * CB;
-  for (int e = t; e < CB * CB; e += 256) L[e >> 6][e & 63] = Ld[(int64_t)i * CB * CB + e];
+  const double* Ld = chol_diag(A, ld, nb, i);
+  for (int e = t; e < CB * CB; e += 256) L[e >> 6][e & 63] = Ld[(e >> 6) * ld + (e & 63)];
   __syncthreads();
   // column c of the inverse, row after row: X[rr] = (e_rr - sum_{k < rr} L[rr][k] X[k]) / L[rr][rr],
   // the sum shared by four threads
@@ -391,10 +404,10 @@ __global__ __launch_bounds__(256) void chol_back_kernel(const double* __restrict
   }
 }
 
-// the matrix with the right-hand side's block row, the diagonal blocks' factors, y
+// the matrix, the right-hand side as its last row, y
 size_t sr_solve_ws_bytes(int64_t B) {
   const int64_t ld = round_up(B, CB);
-  return (size_t)(ld * (ld + CB) * 8 + ld * CB * 8 + round_up(ld * 8, 256));
+  return (size_t)round_up(ld * ld * 8, 256) + 2 * (size_t)round_up(ld * 8, 256);
 }
 
 hipError_t launch_sr_solve(const float* K, int64_t B, double shift, const float* rhs, double scale, float* y,
@@ -402,18 +415,17 @@ hipError_t launch_sr_solve(const float* K, int64_t B, double shift, const float*
   const int64_t ld = round_up(B, CB);
   const int nb = (int)(ld / CB);
   double* A = (double*)ws;
-  double* Ld = A + ld * (ld + CB);
-  unsigned long long* yd = (unsigned long long*)(Ld + ld * CB);
-  chol_init_kernel<<<(unsigned)((ld * (ld + CB) + 255) / 256), 256, 0, st>>>(K, B, ld, shift, rhs, scale, A, yd);
+  unsigned long long* yd = (unsigned long long*)(A + ld * (ld + 1));
+  chol_init_kernel<<<(unsigned)((ld * (ld + 1) + 255) / 256), 256, 0, st>>>(K, B, ld, shift, rhs, scale, A, yd);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   for (int j = -1; j < nb - 1; ++j) {
     // m columns right of j + 1 with their rows down to the right-hand side; none before the first column
     const int64_t m = nb - j - 2, rest = j < 0 ? 0 : m * (m + 1) / 2 + m;
-    chol_step_kernel<<<(unsigned)(nb - j - 1 + rest), 64 * CW, 0, st>>>(A, ld, nb, j, Ld);
+    chol_step_kernel<<<(unsigned)(nb - j - 1 + rest), 64 * CW, 0, st>>>(A, ld, nb, j);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  chol_back_kernel<<<(unsigned)nb, 256, 0, st>>>(A, ld, nb, Ld, yd, B, y);
+  chol_back_kernel<<<(unsigned)nb, 256, 0, st>>>(A, ld, nb, yd, B, y);
   return hipGetLastError();
 }
 
