@@ -699,9 +699,9 @@ static WsLayout layout(int n, int h, int64_t B, int dtype, int which) {
     off += round_up((int64_t)bytes, 256);
     return o;
   };
-  const int pf = dtype == VQMC_BF16 ? 1 : 2;  // FP32 tiles may have 32 rows or columns: twice the partial sums
-  L.R = take((size_t)std::max(B * g.ldh, h * g.ldB) * es);  // FP32 log p keeps it by unit
-  L.lp_part = take((size_t)pf * g.nt_o * B * 4);
+  const int pf = dtype == VQMC_BF16 ? 1 : 2;  // FP32 tiles may have 32 rows: twice the partial sums
+  L.R = take((size_t)B * g.ldh * es);  // FP32 log p: by unit, h x B
+  L.lp_part = take((size_t)g.nt_o * B * 4);
   if (which == 1) {  // backward
     L.Rt = take((size_t)h * g.ldB * es);
     L.G = take((size_t)B * g.ldn * es);
@@ -732,8 +732,8 @@ static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   hipError_t e;
   if constexpr (sizeof(T) == 4) {
     int np = 0;
-    if ((e = launch_f32_hidden(m, S, B, nullptr, R, st)) != hipSuccess) return e;  // by unit, h x ld(B)
-    if ((e = launch_f32_logp(m, S, B, R, lp_part, Z, &np, st)) != hipSuccess) return e;
+    if ((e = launch_f32_hidden(m, S, B, nullptr, R, B, st)) != hipSuccess) return e;  // by unit, h x B
+    if ((e = launch_f32_logp(m, S, B, R, B, lp_part, Z, &np, st)) != hipSuccess) return e;
     sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
     return hipGetLastError();
   } else {
@@ -763,7 +763,7 @@ static hipError_t backward_t(const vqmc_made& m, const int8_t* S, int64_t B, con
   hipError_t e;
   if constexpr (sizeof(T) == 4) {
     int np1 = 0, np2 = 0;
-    if ((e = launch_f32_hidden(m, S, B, R, Rt, st)) != hipSuccess) return e;
+    if ((e = launch_f32_hidden(m, S, B, R, Rt, g.ldB, st)) != hipSuccess) return e;
     // the first product does not read coef; it may overlap the work that produces it
     if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
     if ((e = launch_f32_out_grad(m, S, B, Rt, coef, G, Gt, nullptr, db2_part, &np2, st)) != hipSuccess) return e;
@@ -822,7 +822,7 @@ static hipError_t sr_gram_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if constexpr (sizeof(T) == 4) {
     int np2 = 0;
-    if ((e = launch_f32_hidden(m, S, B, nullptr, Rt, st)) != hipSuccess) return e;
+    if ((e = launch_f32_hidden(m, S, B, nullptr, Rt, g.ldB, st)) != hipSuccess) return e;
     if ((e = launch_f32_out_grad(m, S, B, Rt, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
   } else {
     int np2 = 0;

@@ -413,28 +413,32 @@ static inline unsigned tiles(int64_t x, int t) { return (unsigned)((x + t - 1) /
 // The rule between the two shapes, for an M x N output.
 static bool f32_large(int64_t M, int64_t N) { return (int64_t)tiles(M, 64) * tiles(N, 64) >= 512; }
 
-hipError_t launch_f32_hidden(const vqmc_made& m, const int8_t* S, int64_t B, float* R, float* Rt, hipStream_t st) {
+hipError_t launch_f32_hidden(const vqmc_made& m, const int8_t* S, int64_t B, float* R, float* Rt, int64_t ldr,
+                             hipStream_t st) {
   const int64_t ldn = round_up(m.n, kPad), ldh = round_up(m.h, kPad), ldB = round_up(B, kPad);
   auto go = [&](auto kern, int bm, int bn, int nt) {
     kern<<<dim3(tiles(m.h, bn), tiles(ldB, bm)), nt, 0, st>>>(S, ldn, (const float*)m.P, ldh, m.b1, m.c, m.n, m.h, B, R, Rt,
-                                                              ldB);
+                                                              ldr);
     return hipGetLastError();
   };
   return f32_large(ldB, ldh) ? go(f32_hidden_kernel<FLarge>, FLarge::BM, FLarge::BN, FLarge::NT)
                              : go(f32_hidden_kernel<FSmall>, FSmall::BM, FSmall::BN, FSmall::NT);
 }
 
-hipError_t launch_f32_logp(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, float* lp_part, float* Z,
-                           int* nparts, hipStream_t st) {
+// (32 x 64 tiles where the other products take 32 x 32 ones: half the partial sums, so that the scratch of
+// vqmc_logprob_noalloc goes as far as with 64 x 64 tiles)
+hipError_t launch_f32_logp(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, int64_t ldr, float* lp_part,
+                           float* Z, int* nparts, hipStream_t st) {
   const int64_t ldn = round_up(m.n, kPad), ldB = round_up(B, kPad);
   auto go = [&](auto kern, int bm, int bn, int nt) {
     *nparts = (int)tiles(m.n, bn);
-    kern<<<dim3(tiles(m.n, bn), tiles(B, bm)), nt, 0, st>>>(Rt, ldB, (const float*)m.Pt, ldn, m.b2, m.c, m.n, m.h, B, S,
+    kern<<<dim3(tiles(m.n, bn), tiles(B, bm)), nt, 0, st>>>(Rt, ldr, (const float*)m.Pt, ldn, m.b2, m.c, m.n, m.h, B, S,
                                                             lp_part, Z, nullptr, nullptr, nullptr, nullptr, nullptr);
     return hipGetLastError();
   };
+  using FWide = F32<1, 2, 4>;
   return f32_large(ldB, ldn) ? go(f32_out_kernel<FLarge, false>, FLarge::BM, FLarge::BN, FLarge::NT)
-                             : go(f32_out_kernel<FSmall, false>, FSmall::BM, FSmall::BN, FSmall::NT);
+                             : go(f32_out_kernel<FWide, false>, FWide::BM, FWide::BN, FWide::NT);
 }
 
 hipError_t launch_f32_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, const float* coef,

@@ -88,13 +88,13 @@ hipError_t launch_sr_gram_sweeps(int dtype, const void* Gt, const void* Rt, cons
 size_t sr_solve_ws_bytes(int64_t B);
 hipError_t launch_sr_solve(const float* K, int64_t B, double shift, const float* rhs, double scale, float* y,
                            void* ws, hipStream_t st);
-// gemm_f32.hip: the FP32 products.  R, D: B x ld(h); Rt, Dt: h x ld(B); G: B x ld(n); Gt, St: n x ld(B); the
-// partial sums have at most ld(B) / 32 rows (db2_part of ld(n), db1_part of ld(h)) and ld(n) / 32
+// gemm_f32.hip: the FP32 products.  R, D: B x ld(h); Rt, Dt: h x ld(B) (h x ldr in the first two, ldr >= B); G: B x ld(n); Gt, St: n x ld(B); the
+// partial sums have at most ld(B) / 32 rows (db2_part of ld(n), db1_part of ld(h)) and ld(n) / 64
 // rows of B (lp_part); the number written comes back in np2, np1, nparts.
 hipError_t launch_f32_hidden(const vqmc_made& m, const int8_t* S, int64_t B, float* R /* nullable */, float* Rt,
-                             hipStream_t st);
-hipError_t launch_f32_logp(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, float* lp_part,
-                           float* Z /* nullable */, int* nparts, hipStream_t st);
+                             int64_t ldr, hipStream_t st);
+hipError_t launch_f32_logp(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, int64_t ldr,
+                           float* lp_part, float* Z /* nullable */, int* nparts, hipStream_t st);
 hipError_t launch_f32_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, const float* coef,
                                float* G, float* Gt, float* St /* nullable */, float* db2_part, int* np2, hipStream_t st);
 // D, with R copied from Rt if given, or Dt, the other null
