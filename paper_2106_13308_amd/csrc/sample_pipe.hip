@@ -30,7 +30,14 @@
 //
 // Workgroup = 8 samples, 12 waves.  Waves 0-1 sweep block b, four samples each, lane
 // (sample s, group g) holding sites 4g..4g+3 of sample s (and of the next block) in
-// registers; a unit's dot product is a 16-lane DPP reduction.  The ten helper waves 2-11
+// registers; a unit's dot product is a 16-lane DPP reduction.
+// The sweep issues an instruction every 7 cycles or so whatever depends on what, so its cost is their number: units go
+// in groups of four whose loads of state and constants, stores, bounds and addresses are taken
+// once per group, and the record's loads and the products beside the chain fill the waits of the
+// reduction (345 -> 245 cycles a unit at n = h = 2000, B = 8192: 1285 -> 1025 us; n = 500, h = 193, FP32: 41 ->
+// 34 us).  A load of 16 bytes a lane still costs it about 22 cycles.  Four sweep waves of two samples
+// (the two halves of a wave on one block and the ones beside it) came to 18 000 cycles a block
+// against 17 300, and their helpers lost 15 %.  The ten helper waves 2-11
 // meanwhile push block b-1's spins into the units completing after block b (all helpers),
 // compute the part of block b+1's logits that only needs units complete before block b
 // (helpers 4-9), draw block b+1's uniforms (helpers 0-1) and write out block b-1's spins and
@@ -177,7 +184,6 @@ struct SpRec {
   float4 w2;  // W2, this block
   float4 p1;  // 2 W1, previous block
   float4 n2;  // W2, next block
-  float ns;   // minus the sum of the W1 halves
 };
 
 // TIMING: each wave also counts its cycles (s_memtime) between the per-block barriers.
@@ -285,17 +291,18 @@ __global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
     __builtin_amdgcn_s_setprio(3);
     const int ss = 4 * wv + (lane >> 4), g = lane & 15;
     SpRec ring[SP_PDS];
-    auto fetch_rec = [&](SpRec& r, int u) {
-      const float* q = band + (int64_t)u * SP_REC + 4 * g;
-      r.w1 = *(const float4*)q;
-      r.w2 = *(const float4*)(q + 64);
-      r.p1 = *(const float4*)(q + 128);
-      r.n2 = *(const float4*)(q + 192);
-      // the four copies keep this a per-lane (vector) load
-      r.ns = band[(int64_t)u * SP_REC + 256 + (lane & 3)];
+    // slot p of the ring from the records at byte offset so on (fetches may run up to SP_PDS records past
+    // the last: the tables behind the records are longer than that)
+    const sp_rsrc_t rec = sp_rsrc((const uint8_t*)band, 0x7FFFFFFF);
+    auto fetch = [&](int p, int part, uint32_t so) {
+      return __builtin_bit_cast(float4, sp_ld16(rec, 16 * g + p * SP_REC * 4 + 256 * part, so));
     };
+    // minus the sum of the W1 halves of the units u + lane % 4
+    const int noff = (lane & 3) * (SP_REC * 4) + 1024;
+    auto fetch_ns = [&](int u) { return sp_ld4(rec, noff, (uint32_t)u * (SP_REC * 4)); };
 #pragma unroll
-    for (int p = 0; p < SP_PDS; ++p) fetch_rec(ring[p], min(p, h - 1));
+    for (int p = 0; p < SP_PDS; ++p) ring[p] = SpRec{fetch(p, 0, 0), fetch(p, 1, 0), fetch(p, 2, 0), fetch(p, 3, 0)};
+    float nsn = fetch_ns(0);  // of the next group of units
     float zn[4], cp[4];  // next block's logits from this block's units; previous block's draws
 #pragma unroll
     for (int e = 0; e < 4; ++e) zn[e] = cp[e] = 0.f;
@@ -321,40 +328,88 @@ __global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
 #pragma unroll
         for (int e = 0; e < 4; ++e) zn[e] = 0.f;
       }
-      float a0n = arow[fprev];
-      for (int ub = fprev - fprev % SP_PDS; ub < fcur; ub += SP_PDS) {
+      // Units in groups of SP_PDS from a multiple of it on.  Every step reloads its slot of the ring, so the number
+      // of loads in flight is the same on every path and each use waits only for its own slot: one that
+      // was used takes unit u + PDS; one skipped before the range already holds u + PDS and one skipped
+      // after it holds u, which the next block needs: both reload what they hold.  The barriers keep
+      // the loads after the slot's last use, so they go straight into the slot's registers.
+      // acc1: the previous block's part of the unit's dot product
+      auto beside = [&](const float4& p1) {
+        return fmaf(cp[3], p1.w, fmaf(cp[2], p1.z, fmaf(cp[1], p1.y, fmaf(cp[0], p1.x, 0.f))));
+      };
+      int ub = fprev - fprev % SP_PDS;
+      float4 a4 = *(const float4*)(arow + ub);
+      auto group = [&](bool whole) {
+        const float a0[4] = {a4.x, a4.y, a4.z, a4.w};
+        const float ns = nsn;
+        a4 = *(const float4*)(arow + ub + SP_PDS);  // (past the block's units: not used)
+        nsn = fetch_ns(whole || ub + SP_PDS <= fcur ? ub + SP_PDS : ub);
+        float an[4], rl = 0.f, acc1 = 0.f;
+        if (whole) acc1 = beside(ring[0].p1);
 #pragma unroll
         for (int p = 0; p < SP_PDS; ++p) {
           const int u = ub + p;
-          if (u >= fprev && u < fcur) {
-            const SpRec& r = ring[p];
-            const float a0 = a0n;
-            a0n = arow[u + 1];
-            const float w1[4] = {r.w1.x, r.w1.y, r.w1.z, r.w1.w};
-            const float w2[4] = {r.w2.x, r.w2.y, r.w2.z, r.w2.w};
-            const float p1[4] = {r.p1.x, r.p1.y, r.p1.z, r.p1.w};
-            const float n2[4] = {r.n2.x, r.n2.y, r.n2.z, r.n2.w};
+          SpRec& r = ring[p];
+          const uint32_t next = (uint32_t)(whole || u < fcur ? ub + SP_PDS : ub) * (SP_REC * 4);
+          if (whole || (u >= fprev && u < fcur)) {
             // c_e = 1 if site e is (or would be) drawn +1 now, else 0; w1 and p1 hold 2 W1
-            float acc0 = 0.f, acc1 = 0.f;
+            float c[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float ce = __builtin_amdgcn_fmed3f(fmaf(zr[e], SP_SCALE, tz[e]), 0.f, 1.f);
-              acc0 = fmaf(ce, w1[e], acc0);
-              acc1 = fmaf(cp[e], p1[e], acc1);
+            for (int e = 0; e < 4; ++e) c[e] = __builtin_amdgcn_fmed3f(fmaf(zr[e], SP_SCALE, tz[e]), 0.f, 1.f);
+            const float acc0 = fmaf(c[3], r.w1.w, fmaf(c[2], r.w1.z, fmaf(c[1], r.w1.y, fmaf(c[0], r.w1.x, 0.f))));
+            // The steps of the 16-lane sum wait for one another; in a whole group what they leave
+            // room for is done between them: the next unit's acc1, the previous unit's part of the next
+            // block's logits, and the loads.
+            float acc = acc0 + (whole ? acc1 : beside(r.p1));
+            const int pn = (p + 1) % SP_PDS, pp = p - 1;  // (pp only for p > 0)
+            if (whole) {
+              __builtin_amdgcn_sched_barrier(0);
+              r.w1 = fetch(p, 0, next);
+              r.p1 = fetch(p, 2, next);
+              __builtin_amdgcn_sched_barrier(0);
             }
-            float acc = acc0 + acc1;
             acc += VQMC_DPP(acc, 0xB1);   // quad_perm [1,0,3,2]
-            acc += VQMC_DPP(acc, 0x4E);   // quad_perm [2,3,0,1]
-            acc += VQMC_DPP(acc, 0x141);  // row_half_mirror
-            acc += VQMC_DPP(acc, 0x140);  // row_mirror: 16-lane total in every lane
-            const float a = (acc + r.ns) + a0;
-            const float rl = fmaxf(a, 0.f);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              zr[e] = fmaf(w2[e], rl, zr[e]);
-              zn[e] = fmaf(n2[e], rl, zn[e]);
+            if (whole) {
+              __builtin_amdgcn_sched_barrier(0);
+              acc1 = fmaf(cp[0], ring[pn].p1.x, 0.f);
+              if (p > 0) zn[0] = fmaf(ring[pp].n2.x, rl, zn[0]);
+              __builtin_amdgcn_sched_barrier(0);
             }
-            arow[u] = a;
+            acc += VQMC_DPP(acc, 0x4E);   // quad_perm [2,3,0,1]
+            if (whole) {
+              __builtin_amdgcn_sched_barrier(0);
+              acc1 = fmaf(cp[1], ring[pn].p1.y, acc1);
+              if (p > 0) zn[1] = fmaf(ring[pp].n2.y, rl, zn[1]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            acc += VQMC_DPP(acc, 0x141);  // row_half_mirror
+            if (whole) {
+              __builtin_amdgcn_sched_barrier(0);
+              acc1 = fmaf(cp[2], ring[pn].p1.z, acc1);
+              if (p > 0) zn[2] = fmaf(ring[pp].n2.z, rl, zn[2]);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            acc += VQMC_DPP(acc, 0x140);  // row_mirror: 16-lane total in every lane
+            if (whole) {
+              __builtin_amdgcn_sched_barrier(0);
+              acc1 = fmaf(cp[3], ring[pn].p1.w, acc1);
+              if (p > 0) {
+                zn[3] = fmaf(ring[pp].n2.w, rl, zn[3]);
+                ring[pp].n2 = fetch(pp, 3, next);
+              }
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            const float nu = p == 0 ? VQMC_DPP(ns, 0x00) : p == 1 ? VQMC_DPP(ns, 0x55) : p == 2 ? VQMC_DPP(ns, 0xAA) : VQMC_DPP(ns, 0xFF);
+            const float a = (acc + nu) + a0[p];
+            rl = fmaxf(a, 0.f);
+            zr[0] = fmaf(r.w2.x, rl, zr[0]); zr[1] = fmaf(r.w2.y, rl, zr[1]);
+            zr[2] = fmaf(r.w2.z, rl, zr[2]); zr[3] = fmaf(r.w2.w, rl, zr[3]);
+            if (!whole || p == SP_PDS - 1) {
+              zn[0] = fmaf(r.n2.x, rl, zn[0]); zn[1] = fmaf(r.n2.y, rl, zn[1]);
+              zn[2] = fmaf(r.n2.z, rl, zn[2]); zn[3] = fmaf(r.n2.w, rl, zn[3]);
+            }
+            an[p] = a;
+            if (!whole) arow[u] = a;
             if constexpr (PLANES) {
               // exact three-term split of relu(a) by truncation (see sp_split3)
               const uint32_t x = __float_as_uint(rl);
@@ -367,16 +422,20 @@ __global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
               q[2 * SP_MS * PLDA] = (bf16_t)(__float_as_uint(r2) >> 16);
             }
           }
-          // Every step reloads its slot, so the number of loads in flight is the same on
-          // every path and each use waits only for its own slot.  A slot that was used
-          // takes unit u + PDS; a slot skipped before the range already holds u + PDS and
-          // one skipped after it holds u, which the next block needs: both reload what
-          // they hold.  The barrier keeps the loads after the slot's last use, so they go
-          // straight into the slot's registers.
           __builtin_amdgcn_sched_barrier(0);
-          fetch_rec(ring[p], min(u < fcur ? u + SP_PDS : u, h - 1));
+          if (!whole) {
+            r.w1 = fetch(p, 0, next);
+            r.p1 = fetch(p, 2, next);
+          }
+          r.w2 = fetch(p, 1, next);
+          if (!whole || p == SP_PDS - 1) r.n2 = fetch(p, 3, next);
         }
-      }
+        if (whole) *(float4*)(arow + ub) = make_float4(an[0], an[1], an[2], an[3]);
+        ub += SP_PDS;
+      };
+      if (ub < fprev) group(false);
+      while (ub + SP_PDS <= fcur) group(true);
+      if (ub < fcur) group(false);
       // decisions, spins and s*z of the block
       uint32_t word = 0, bw[2] = {0u, 0u};
       float zsv[4];
