@@ -15,9 +15,9 @@ namespace vqmc {
 // ---------------------------------------------------------------- sparse (CSR upper)
 // One workgroup of 1024 threads handles EMSE samples.  Their spins are staged in LDS as
 // one byte per site (bit q = [s_q = +1]), so an edge costs one byte read for all samples,
-// and so is the row pointer (int32) when it fits.  Thread t walks rows i = t, t + 1024,
-// ..., two edges per step with their loads issued together.  Row i of the upper triangle
-// contributes
+// and so is the row pointer (int32) when it fits.  A group of `lanes` threads walks rows i, i + groups, ..., each
+// its share of a row's edges, two per step with their loads issued together.  Row i of the upper triangle
+// contributes (each lane the sums over its share)
 //   s_iq sum_j w_ij s_jq = s_iq (2 Y_q - W_i),  Y_q = sum_j w_ij [s_jq = +1],  W_i = sum_j w_ij,
 // accumulated exactly in int64 (integer weights) or in double (float weights, whose sums
 // of exact terms only differ from the oracle's by summation order).  A fixed thread -> row
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bits_kernel(int n, int6
                                                                     const int32_t* __restrict__ col,
                                                                     const WT* __restrict__ w,
                                                                     const int8_t* __restrict__ S, int64_t B,
-                                                                    int nst, AT* __restrict__ E) {
+                                                                    int nst, int lanes, AT* __restrict__ E) {
   // nst bytes of site bits, then the row pointer (n + 1 int32, if staged), then scratch
   extern __shared__ __attribute__((aligned(16))) uint8_t shb[];
   uint8_t* bits = shb;
@@ -70,17 +70,18 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bits_kernel(int n, int6
   // sum can overflow; a row beyond that is summed again in int64), else AT
   constexpr bool INT = std::is_integral<WT>::value;
   typedef typename std::conditional<INT, int32_t, AT>::type RT;
-  for (int i = t; i < n; i += EB_THREADS) {
-    const int64_t e0 = rowp(i), e1 = rowp(i + 1);
+  const int groups = EB_THREADS / lanes, sub = t & (lanes - 1);
+  for (int i = t / lanes; i < n; i += groups) {
+    const int64_t e0 = rowp(i) + sub, e1 = rowp(i + 1);  // the lane's edges: e0, e0 + lanes, ..
     RT y[EMSE];
 #pragma unroll
     for (int q = 0; q < EMSE; ++q) y[q] = 0;
     AT wsum = 0;
     int64_t wabs = 0;
     int64_t e = e0;
-    for (; e + 1 < e1; e += 2) {  // two edges per step: their loads are issued together
-      const int j0 = col[e], j1 = col[e + 1];
-      const RT w0 = (RT)w[e], w1 = (RT)w[e + 1];
+    for (; e + lanes < e1; e += 2 * lanes) {  // two edges per step: their loads are issued together
+      const int j0 = col[e], j1 = col[e + lanes];
+      const RT w0 = (RT)w[e], w1 = (RT)w[e + lanes];
       const uint32_t m0 = bits[j0], m1 = bits[j1];
       wsum += (AT)w0 + (AT)w1;
       if constexpr (INT) wabs += llabs((int64_t)w0) + llabs((int64_t)w1);
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bits_kernel(int n, int6
     if (INT && wabs > (int64_t)INT32_MAX) {
 #pragma unroll
       for (int q = 0; q < EMSE; ++q) ya[q] = 0;
-      for (int64_t f = e0; f < e1; ++f) {
+      for (int64_t f = e0; f < e1; f += lanes) {
         const AT wf = (AT)w[f];
         const uint32_t mf = bits[col[f]];
 #pragma unroll
@@ -134,18 +135,29 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bits_kernel(int n, int6
 }
 
 // ---------------------------------------------------------------- sparse, byte lanes
-// Integer weights, same rows and sums as above, with each site staged as eight bytes (byte q =
-// [s_q = +1]) instead of eight bits: then w * site adds w to all eight samples' row sums Y_q at
-// once, each in its own byte, as two 32-bit multiply-adds per edge.  A byte holds Y_q exactly
-// while the row's weights are non-negative and sum to at most 255 (every Max-Cut graph with
-// small integer weights); a row outside that range is summed again sample by sample.
+// Integer weights, each site staged as eight bytes (byte q = 0xFF where s_q = +1, else 0) instead of
+// eight bits.  An edge adds w s_i s_j = w - 2 w [s_i != s_j], so
+//   E_q = W - 2 Y_q,   Y_q = sum_edges w [s_iq != s_jq],   W = sum_edges w,
+// and (w in every byte) & (site i ^ site j) holds w or 0 for all eight samples, to be added byte by byte.
+// No edge needs its row's sum, so L lanes share a row with nothing to add up between
+// them (L from the mean row length: a lane gets 8 to 16 edges of a row, or one lane a whole row), and the
+// bytes run on across rows; they are added to 64-bit sums before the weights in them exceed 255.
+// Edges with weights outside [0, 255] go to those sums directly.
+//
+// What bounds it: the address coalescing of the rows' loads (16 cycles a load instruction when the lanes lie
+// apart), then their latency.  So a lane takes four edges by one 16-byte load of each array, and
+// four rows at a time with their loads issued together.  Measured (us; before: a thread per row, two
+// edges a step, 64-bit sums per row): n = 500, 75 % of the edges, B = 1024: 35 -> 18; n = 10000, degree 10, B = 2048:
+// 41 -> 30.
+constexpr int EC_RB = 4;
+constexpr int EC_U = 4;
 template <bool RP_LDS>
 __global__ __launch_bounds__(EB_THREADS) void energy_csr_bytes_kernel(int n, int64_t lds,
                                                                      const int64_t* __restrict__ rowptr,
                                                                      const int32_t* __restrict__ col,
-                                                                     const int32_t* __restrict__ w,
+                                                                     const int32_t* __restrict__ w, int64_t nnz,
                                                                      const int8_t* __restrict__ S, int64_t B,
-                                                                     int nsp, int64_t* __restrict__ E) {
+                                                                     int nsp, int lanes, int64_t* __restrict__ E) {
   // nsp uint2 site words (n rounded up to 16), then the row pointer (n + 1 int32, if staged),
   // then scratch
   extern __shared__ __attribute__((aligned(16))) uint8_t shb[];
@@ -155,91 +167,128 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bytes_kernel(int n, int
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int64_t b0 = (int64_t)blockIdx.x * EMSE;
   const int nq = (int)min<int64_t>(EMSE, B - b0);
-  // sixteen sites per item: one 16-byte piece of each sample's row (inside the padded row),
-  // gathered into a bit per sample, then spread to a byte per sample
-  for (int c0 = t; c0 < nsp / 16; c0 += EB_THREADS) {
-    uint32_t a[4] = {0u, 0u, 0u, 0u};
+  // four sites per item (of sixteen, the lanes' stores would all meet in one LDS bank): a word of
+  // each sample's row, gathered into a bit per sample, then spread to a byte per sample
+  for (int c0 = t; c0 < nsp / 4; c0 += EB_THREADS) {
+    uint32_t a = 0u;
 #pragma unroll
-    for (int q = 0; q < EMSE; ++q) {
-      if (q < nq) {
-        const uint4 v = *(const uint4*)(S + (b0 + q) * lds + 16 * c0);
-        a[0] |= ((~v.x >> 7) & 0x01010101u) << q;
-        a[1] |= ((~v.y >> 7) & 0x01010101u) << q;
-        a[2] |= ((~v.z >> 7) & 0x01010101u) << q;
-        a[3] |= ((~v.w >> 7) & 0x01010101u) << q;
-      }
-    }
+    for (int q = 0; q < EMSE; ++q)
+      if (q < nq) a |= ((~*(const uint32_t*)(S + (b0 + q) * lds + 4 * c0) >> 7) & 0x01010101u) << q;
+    uint32_t x[8];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const uint32_t m = (a[e >> 2] >> (8 * (e & 3))) & 0xFFu;
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t m = (a >> (8 * e)) & 0xFFu;
       // bit k of a 4-bit value to bit 8k: the four shifted copies (x 1, 2^7, 2^14, 2^21) do not
-      // overlap, so the product carries nothing
-      sw[16 * c0 + e] = make_uint2(((m & 0xFu) * 0x00204081u) & 0x01010101u, ((m >> 4) * 0x00204081u) & 0x01010101u);
+      // overlap, so the product carries nothing; then the bit to the whole byte
+      x[2 * e] = (((m & 0xFu) * 0x00204081u) & 0x01010101u) * 0xFFu;
+      x[2 * e + 1] = (((m >> 4) * 0x00204081u) & 0x01010101u) * 0xFFu;
     }
+    *(uint4*)(sw + 4 * c0) = make_uint4(x[0], x[1], x[2], x[3]);
+    *(uint4*)(sw + 4 * c0 + 2) = make_uint4(x[4], x[5], x[6], x[7]);
   }
   if constexpr (RP_LDS)
     for (int i = t; i <= n; i += EB_THREADS) rp[i] = (int32_t)rowptr[i];
   __syncthreads();
-  auto rowp = [&](int i) -> int64_t {
-    if constexpr (RP_LDS) return rp[i];
-    else return rowptr[i];
+  auto rowp = [&](int i) -> uint32_t {  // nnz < 2^31
+    if constexpr (RP_LDS) return (uint32_t)rp[i];
+    else return (uint32_t)rowptr[i];
   };
-  int64_t acc[EMSE];
+  int64_t y[EMSE], wsum = 0;
 #pragma unroll
-  for (int q = 0; q < EMSE; ++q) acc[q] = 0;
-  for (int i = t; i < n; i += EB_THREADS) {
-    const int64_t e0 = rowp(i), e1 = rowp(i + 1);
-    uint32_t ylo = 0u, yhi = 0u;  // Y_q in byte q (q < 4 in ylo)
-    int64_t wsum = 0;
-    bool small = true;
-    int64_t e = e0;
-    for (; e + 1 < e1; e += 2) {  // two edges per step: their loads are issued together
-      const int j0 = col[e], j1 = col[e + 1];
-      const int32_t w0 = w[e], w1 = w[e + 1];
-      const uint2 s0 = sw[j0], s1 = sw[j1];
-      wsum += (int64_t)w0 + (int64_t)w1;
-      small = small && (uint32_t)w0 <= 255u && (uint32_t)w1 <= 255u;
-      ylo += (uint32_t)w0 * s0.x + (uint32_t)w1 * s1.x;
-      yhi += (uint32_t)w0 * s0.y + (uint32_t)w1 * s1.y;
+  for (int q = 0; q < EMSE; ++q) y[q] = 0;
+  uint32_t ylo = 0u, yhi = 0u, held = 0u;  // Y_q in byte q (q < 4 in ylo), and the weights in them
+  auto flush = [&]() {
+#pragma unroll
+    for (int q = 0; q < EMSE; ++q) y[q] += ((q < 4 ? ylo : yhi) >> (8 * (q & 3))) & 0xFFu;
+    ylo = yhi = held = 0u;
+  };
+  const int groups = EB_THREADS / lanes, sub = t & (lanes - 1);
+  const __amdgpu_buffer_rsrc_t rcol = __builtin_amdgcn_make_buffer_rsrc((void*)col, 0, (int)(uint32_t)(4 * nnz), 0x00020000);
+  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc((void*)w, 0, (int)(uint32_t)(4 * nnz), 0x00020000);
+  const uint32_t last = (uint32_t)nnz - EC_U;  // nnz >= EC_U: the last place for a load
+  for (int i0 = t / lanes; i0 < n; i0 += EC_RB * groups) {
+    uint32_t e[EC_RB], e1[EC_RB];
+    int left = 0;
+    uint2 si[EC_RB];
+#pragma unroll
+    for (int r = 0; r < EC_RB; ++r) {
+      const int i = i0 + r * groups, ic = min(i, n - 1);
+      e[r] = rowp(ic) + EC_U * sub;
+      e1[r] = i < n ? rowp(ic + 1) : e[r];
+      si[r] = sw[ic];
+      left = max(left, (int)(e1[r] - e[r]));
     }
-    if (e < e1) {
-      const int32_t w0 = w[e];
-      const uint2 s0 = sw[col[e]];
-      wsum += (int64_t)w0;
-      small = small && (uint32_t)w0 <= 255u;
-      ylo += (uint32_t)w0 * s0.x;
-      yhi += (uint32_t)w0 * s0.y;
-    }
-    int64_t ya[EMSE];
-    if (small && wsum <= 255) {
+    for (; left > 0; left -= EC_U * lanes) {
+      uint32_t j[EC_RB][EC_U], wt[EC_RB][EC_U];
 #pragma unroll
-      for (int q = 0; q < EMSE; ++q) ya[q] = (int64_t)(((q < 4 ? ylo : yhi) >> (8 * (q & 3))) & 0xFFu);
-    } else {  // the row again, one int64 sum per sample
-#pragma unroll
-      for (int q = 0; q < EMSE; ++q) ya[q] = 0;
-      for (int64_t f = e0; f < e1; ++f) {
-        const int64_t wf = w[f];
-        const uint2 sf = sw[col[f]];
-#pragma unroll
-        for (int q = 0; q < EMSE; ++q) ya[q] += (((q < 4 ? sf.x : sf.y) >> (8 * (q & 3))) & 1u) ? wf : 0;
+      for (int r = 0; r < EC_RB; ++r) {
+        const int at = (int)(min(e[r], last) * 4u);
+        const uint4 c4 = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rcol, at, 0, 0));
+        const uint4 w4 = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, at, 0, 0));
+        j[r][0] = c4.x; j[r][1] = c4.y; j[r][2] = c4.z; j[r][3] = c4.w;
+        wt[r][0] = w4.x; wt[r][1] = w4.y; wt[r][2] = w4.z; wt[r][3] = w4.w;
       }
-    }
-    const uint2 si = sw[i];
+      uint32_t all = 0u, sum = 0u;
 #pragma unroll
-    for (int q = 0; q < EMSE; ++q) {
-      const int64_t r = 2 * ya[q] - wsum;
-      acc[q] += (((q < 4 ? si.x : si.y) >> (8 * (q & 3))) & 1u) ? r : -r;
+      for (int r = 0; r < EC_RB; ++r) {
+        // the edges e .. e1 - 1 among those loaded
+        const uint32_t off = min(e[r], last) - e[r], len = (int)(e1[r] - e[r]) > 0 ? e1[r] - e[r] : 0u;
+#pragma unroll
+        for (int u = 0; u < EC_U; ++u) {
+          wt[r][u] = off + u < len ? wt[r][u] : 0u;
+          all |= wt[r][u];
+          sum += wt[r][u];
+        }
+      }
+      if (all <= 255u && sum <= 255u) {
+        if (held + sum > 255u) flush();
+        held += sum;
+        wsum += sum;
+#pragma unroll
+        for (int r = 0; r < EC_RB; ++r)
+#pragma unroll
+          for (int u = 0; u < EC_U; ++u) {
+            const uint2 sj = sw[j[r][u]];
+            const uint32_t w4 = __builtin_amdgcn_perm(0u, wt[r][u], 0u);  // byte 0 in all four
+            ylo += w4 & (si[r].x ^ sj.x);
+            yhi += w4 & (si[r].y ^ sj.y);
+          }
+      } else {
+#pragma unroll
+        for (int r = 0; r < EC_RB; ++r)
+#pragma unroll
+          for (int u = 0; u < EC_U; ++u) {
+            const uint2 sj = sw[j[r][u]];
+            const uint32_t dx = si[r].x ^ sj.x, dy = si[r].y ^ sj.y;
+            const int64_t we = (int32_t)wt[r][u];
+            wsum += we;
+#pragma unroll
+            for (int q = 0; q < EMSE; ++q) y[q] += (((q < 4 ? dx : dy) >> (8 * (q & 3))) & 1u) ? we : 0;
+          }
+      }
+#pragma unroll
+      for (int r = 0; r < EC_RB; ++r) e[r] += EC_U * lanes;
     }
   }
-  // per sample: fixed butterfly over the wave, then the sixteen waves in order
+  flush();
+  // E_q of the lane, then the sums over the wave: three exchanges that halve the samples a lane holds,
+  // three over the eight lanes with the same sample, then the sixteen waves in order
+#pragma unroll
+  for (int q = 0; q < EMSE; ++q) y[q] = wsum - 2 * y[q];
+#pragma unroll
+  for (int k = 4; k > 0; k >>= 1) {
+    const bool up = lane & (8 * k);
+#pragma unroll
+    for (int q = 0; q < k; ++q) {
+      const int64_t mine = up ? y[q + k] : y[q], theirs = up ? y[q] : y[q + k];
+      y[q] = mine + __shfl_xor(theirs, 8 * k);
+    }
+  }
+  int64_t v = y[0];
+#pragma unroll
+  for (int o = 4; o > 0; o >>= 1) v += __shfl_xor(v, o);
   constexpr int NW = EB_THREADS / 64;
-#pragma unroll
-  for (int q = 0; q < EMSE; ++q) {
-    int64_t v = acc[q];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-    if (lane == 0) red[q * NW + wv] = v;
-  }
+  if ((lane & 7) == 0) red[(lane >> 3) * NW + wv] = v;  // sample 4 [lane & 32] + 2 [lane & 16] + [lane & 8]
   __syncthreads();
   if (t < nq) {
     int64_t s = 0;
@@ -524,23 +573,29 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
   const size_t shbytes = (size_t)nst + (rp_lds ? rpb : 0) + redb;
   const unsigned grid = (unsigned)((B + EMSE - 1) / EMSE);
   hipError_t e;
+  // lanes that share a row: 8 to 16 edges each on average, one lane below 16 edges a row (float weights, n = 1001,
+  // mean row 125, B = 1024: 66 us, 138 with one lane, 87 with 4 to 8 edges; mean row 10: 14 us with one
+  // lane, 18 with four, each of which repeats the row's start and end)
+  int lanes = 1;
+  while (lanes < 64 && (int64_t)16 * lanes * n <= H.nnz) lanes *= 2;
   auto go = [&](auto kern, auto wptr, auto eptr) {
     e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shbytes);
     if (e != hipSuccess) return;
-    kern<<<grid, EB_THREADS, shbytes, st>>>(n, lds, H.rowptr, H.col, wptr, S, B, nst, eptr);
+    kern<<<grid, EB_THREADS, shbytes, st>>>(n, lds, H.rowptr, H.col, wptr, S, B, nst, lanes, eptr);
     e = hipGetLastError();
   };
   if (H.kind == VQMC_H_CSR_INT) {
     // byte lanes when the site words fit in one CU's LDS (the row pointer too if it fits)
     const size_t swb = (size_t)nst * 8;
-    if (H.nnz < (int64_t)1 << 31 && swb + redb <= 160 * 1024) {
+    if (H.nnz >= EC_U && H.nnz < (int64_t)1 << 30 && swb + redb <= 160 * 1024) {
       const bool rpl = swb + rpb + redb <= 160 * 1024;
       const size_t sb = swb + (rpl ? rpb : 0) + redb;
       auto kern = rpl ? energy_csr_bytes_kernel<true> : energy_csr_bytes_kernel<false>;
       if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sb)) !=
           hipSuccess)
         return e;
-      kern<<<grid, EB_THREADS, sb, st>>>(n, lds, H.rowptr, H.col, (const int32_t*)H.w, S, B, nst, (int64_t*)E);
+      kern<<<grid, EB_THREADS, sb, st>>>(n, lds, H.rowptr, H.col, (const int32_t*)H.w, H.nnz, S, B, nst, lanes,
+                                         (int64_t*)E);
       return hipGetLastError();
     }
     if (rp_lds) go(energy_csr_bits_kernel<int32_t, int64_t, true>, (const int32_t*)H.w, (int64_t*)E);
