@@ -732,7 +732,7 @@ static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   hipError_t e;
   if constexpr (sizeof(T) == 4) {
     int np = 0;
-    if ((e = launch_f32_hidden(m, S, B, nullptr, R, B, st)) != hipSuccess) return e;  // by unit, h x B
+    if ((e = launch_f32_hidden(m, S, B, nullptr, R, B, false, st)) != hipSuccess) return e;  // by unit, h x B
     if ((e = launch_f32_logp(m, S, B, R, B, lp_part, Z, &np, st)) != hipSuccess) return e;
     sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
     return hipGetLastError();
@@ -763,7 +763,7 @@ static hipError_t backward_t(const vqmc_made& m, const int8_t* S, int64_t B, con
   hipError_t e;
   if constexpr (sizeof(T) == 4) {
     int np1 = 0, np2 = 0;
-    if ((e = launch_f32_hidden(m, S, B, R, Rt, g.ldB, st)) != hipSuccess) return e;
+    if ((e = launch_f32_hidden(m, S, B, R, Rt, g.ldB, true, st)) != hipSuccess) return e;
     // the first product does not read coef; it may overlap the work that produces it
     if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
     if ((e = launch_f32_out_grad(m, S, B, Rt, coef, G, Gt, nullptr, db2_part, &np2, st)) != hipSuccess) return e;
@@ -822,7 +822,7 @@ static hipError_t sr_gram_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if constexpr (sizeof(T) == 4) {
     int np2 = 0;
-    if ((e = launch_f32_hidden(m, S, B, nullptr, Rt, g.ldB, st)) != hipSuccess) return e;
+    if ((e = launch_f32_hidden(m, S, B, nullptr, Rt, g.ldB, true, st)) != hipSuccess) return e;
     if ((e = launch_f32_out_grad(m, S, B, Rt, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
   } else {
     int np2 = 0;

@@ -158,10 +158,10 @@ struct FCols {
 };
 
 // Spins by sample as the first operand with the sites as ks: S[row][k], columns past n meet masked
-// weights.  Lanes 2 r and 2 r + 1 read 32 bytes of row r; lane (r, g) takes lane 2 r + g's sixteen.
+// weights.  Lanes 2 r and 2 r + 1 read 32 bytes of row r; lane (r, g) takes the even (g = 0) or odd ones.
 struct FSpinRows {
   static constexpr int KC = 32;
-  __device__ static int k(int s, int g) { return 16 * g + s; }
+  __device__ static int k(int s, int g) { return 2 * s + g; }
   using Raw = uint4;
   const int8_t* p;
   __device__ FSpinRows(const int8_t* S, int64_t lds, int64_t row0, int64_t rows) {
@@ -176,13 +176,13 @@ struct FSpinRows {
     v = make_uint4(b.x[0], b.x[1], b.x[2], b.x[3]);
   }
   __device__ void values(const Raw& x, float (&v)[KC / 2]) const {
-    const int lane = threadIdx.x & 63, src = 4 * (2 * (lane & 31) + (lane >> 5));
+    const int lane = threadIdx.x & 63, g = lane >> 5;
     const uint32_t w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t u = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)w[q]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[4 * q + e] = (float)(int8_t)(u >> (8 * e));
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t u = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (2 * (lane & 31) + (q >> 2)), (int)w[q & 3]) >> (8 * g);
+      v[2 * q] = (float)(int8_t)u;
+      v[2 * q + 1] = (float)(int8_t)(u >> 16);
     }
   }
 };
@@ -413,14 +413,22 @@ static inline unsigned tiles(int64_t x, int t) { return (unsigned)((x + t - 1) /
 // The rule between the two shapes, for an M x N output.
 static bool f32_large(int64_t M, int64_t N) { return (int64_t)tiles(M, 64) * tiles(N, 64) >= 512; }
 
+// ordered: no split of K.  A product is then a chain of multiply-adds in the order of the sites, whatever the tile,
+// and the pre-activations are those of the staged engine to the last bit: the gradient's mask [A > 0] must
+// not depend on the path.  log p does not see the last bit's sign and splits K.
 hipError_t launch_f32_hidden(const vqmc_made& m, const int8_t* S, int64_t B, float* R, float* Rt, int64_t ldr,
-                             hipStream_t st) {
+                             bool ordered, hipStream_t st) {
   const int64_t ldn = round_up(m.n, kPad), ldh = round_up(m.h, kPad), ldB = round_up(B, kPad);
   auto go = [&](auto kern, int bm, int bn, int nt) {
     kern<<<dim3(tiles(m.h, bn), tiles(ldB, bm)), nt, 0, st>>>(S, ldn, (const float*)m.P, ldh, m.b1, m.c, m.n, m.h, B, R, Rt,
                                                               ldr);
     return hipGetLastError();
   };
+  using FOne = F32<1, 1, 1>;
+  using FFour = F32<2, 2, 1>;
+  if (ordered)
+    return f32_large(ldB, ldh) ? go(f32_hidden_kernel<FFour>, FFour::BM, FFour::BN, FFour::NT)
+                               : go(f32_hidden_kernel<FOne>, FOne::BM, FOne::BN, FOne::NT);
   return f32_large(ldB, ldh) ? go(f32_hidden_kernel<FLarge>, FLarge::BM, FLarge::BN, FLarge::NT)
                              : go(f32_hidden_kernel<FSmall>, FSmall::BM, FSmall::BN, FSmall::NT);
 }

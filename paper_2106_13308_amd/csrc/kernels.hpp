@@ -92,7 +92,7 @@ hipError_t launch_sr_solve(const float* K, int64_t B, double shift, const float*
 // partial sums have at most ld(B) / 32 rows (db2_part of ld(n), db1_part of ld(h)) and ld(n) / 64
 // rows of B (lp_part); the number written comes back in np2, np1, nparts.
 hipError_t launch_f32_hidden(const vqmc_made& m, const int8_t* S, int64_t B, float* R /* nullable */, float* Rt,
-                             int64_t ldr, hipStream_t st);
+                             int64_t ldr, bool ordered, hipStream_t st);
 hipError_t launch_f32_logp(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, int64_t ldr,
                            float* lp_part, float* Z /* nullable */, int* nparts, hipStream_t st);
 hipError_t launch_f32_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, const float* Rt, const float* coef,
