@@ -20,20 +20,23 @@
 // The staircase masks touch only the stages between the first and the last limit of the tile's rows:
 // there the weight operand is masked in registers, elsewhere it is used as loaded (no masked copies).
 //
-// What bounds it: the run of stages of one tile (0.25 - 0.45 us each: barrier, operand reads, products; the
-// loads at 40 - 50 of the 128 GB/s that a CU's loads into LDS reach), then, for short runs, the tile's start
-// and epilogue.  So long runs take small tiles (more of them at once, long and short ranges paired on a
-// CU) until the tiles fill the chip several times; there and in the weight gradient, whose runs are all
-// alike, large tiles halve the operand reads per product.  Measured (us; before: operands staged through
-// registers, conversions and masks in the loop; adjoint and weights of a step: 64 x 128 and 128 x 128
-// tiles on a masked copy of P^T, all three operands' stages read without overlap of tiles):
+// What bounds it: the chain of stages of one tile.  The longest column of tiles launched alone takes 43 of the first
+// layer's 48 us and 50 of the adjoint's 54 (157 stages of 0.3 us: barrier, operand reads, products, the
+// issue of the next loads, which move 40 - 50 of the 128 GB/s that a CU's loads into LDS can);
+// deeper rings, two stages per barrier, twice the waves and operands read a stage ahead change nothing.
+// For short runs it is a tile's start and epilogue.  So long runs take small tiles (more of
+// them at once, long and short ranges paired on a CU) until the tiles fill the chip several times; there
+// and in the weight gradient, whose runs are all alike, large tiles halve the operand reads per product.
+// Both halves of a stage read as one set of operands cost the large adjoint 96 us instead of 70 below.
+// Measured (us; before: operands staged through registers, conversions and masks in the loop; adjoint and
+// weights of a step: 64 x 128 and 128 x 128 tiles on a masked copy of P^T):
 //                               n = 10000, h = 1000,   n = 3001, h = 611,   n = h = 2000,
 //                               B = 2048               B = 1500             B = 8192
-//   first layer                 48 (282)               20 (94)              82
-//   second layer, log p         54 (157)               17 (35)              78
-//   second layer, gradient                             22 (48)
-//   hidden adjoint              56 (70)                18 (66)              67 (75)
-//   weight and bias gradients   67 (78)                17 (72 + 9)          115 (123)
+//   first layer                 48 (282)               21 (94)              82
+//   second layer, log p         53 (157)               17 (35)              78
+//   second layer, gradient                             21 (48)
+//   hidden adjoint              54 (70)                18 (66)              70 (75)
+//   weight and bias gradients   66 (78)                16 (72 + 9)          113 (123)
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -165,53 +168,44 @@ struct BE {
     return (bf16x8_t){a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
   }
 
-  // the operands of a stage: its two K halves
+  // the operands of half ks of a stage (32 ks)
   struct Frags {
-    bf16x8_t a[2][SPIN ? 1 : FM], b[2][FN];
-    uint2 raw[2][SPIN ? FM : 1];
+    bf16x8_t a[FM], b[FN];
+    uint2 raw[FM];
   };
-  __device__ static void read(const uint4* st, const Lanes& L, Frags& f) {
+  __device__ static void read(const uint4* st, const Lanes& L, int ks, Frags& f) {
     const uint8_t* s = (const uint8_t*)st;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        if constexpr (SPIN) f.raw[ks][i] = *(const uint2*)(s + L.fa[ks] + i * 16 * 64);
-        else f.a[ks][i] = *(const bf16x8_t*)(s + L.fa[ks] + i * 16 * 128);
-      }
-#pragma unroll
-      for (int j = 0; j < FN; ++j) f.b[ks][j] = *(const bf16x8_t*)(s + L.fb[ks] + j * 16 * 128);
+    for (int i = 0; i < FM; ++i) {
+      if constexpr (SPIN) f.raw[i] = *(const uint2*)(s + L.fa[ks] + i * 16 * 64);
+      else f.a[i] = *(const bf16x8_t*)(s + L.fa[ks] + i * 16 * 128);
     }
+#pragma unroll
+    for (int j = 0; j < FN; ++j) f.b[j] = *(const bf16x8_t*)(s + L.fb[ks] + j * 16 * 128);
   }
-  // masks the weights of the stage from K column k on and clears its steps outside the range (both
+  // masks the weights of the half whose first K column is k0 and clears it if it lies outside the range (both
   // operands: an infinity there must not become a NaN), without branches, so the sums stay in place
-  __device__ static void mask(Frags& f, int k, const Range& q, const int (&limit)[FN]) {
+  __device__ static void mask(Frags& f, int k0, const Range& q, const int (&limit)[FN]) {
+    const uint32_t in = k0 >= q.kbeg && k0 < q.kend ? ~0u : 0u;
+    if constexpr (!SPIN) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int k0 = k + 32 * ks;
-      const uint32_t in = k0 >= q.kbeg && k0 < q.kend ? ~0u : 0u;
-      if constexpr (!SPIN) {
+      for (int i = 0; i < FM; ++i) f.a[i] = keep_if(f.a[i], in);
+    }
 #pragma unroll
-        for (int i = 0; i < FM; ++i) f.a[ks][i] = keep_if(f.a[ks][i], in);
-      }
-#pragma unroll
-      for (int j = 0; j < FN; ++j) {
-        f.b[ks][j] = keep_if(f.b[ks][j], in);
-        if constexpr (MASK != B_ALL) f.b[ks][j] = masked(f.b[ks][j], k0 + 8 * (int)((threadIdx.x & 63) >> 4), limit[j]);
-      }
+    for (int j = 0; j < FN; ++j) {
+      f.b[j] = keep_if(f.b[j], in);
+      if constexpr (MASK != B_ALL) f.b[j] = masked(f.b[j], k0 + 8 * (int)((threadIdx.x & 63) >> 4), limit[j]);
     }
   }
-  __device__ static void multiply(const Frags& f, floatx4_t (&acc)[FM][FN]) {
+  __device__ static void multiply(Frags& f, floatx4_t (&acc)[FM][FN]) {
+    if constexpr (SPIN) {
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+      for (int i = 0; i < FM; ++i) f.a[i] = spins(f.raw[i]);
+    }
 #pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        bf16x8_t a;
-        if constexpr (SPIN) a = spins(f.raw[ks][i]);
-        else a = f.a[ks][i];
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, f.b[ks][j], acc[i][j], 0, 0, 0);
-      }
+      for (int j = 0; j < FN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
   }
 
   // Starts the run: fetches its first NS - 1 stages, from column k on (ld columns in all, so before the end
@@ -248,10 +242,13 @@ struct BE {
       b_stage_barrier<(NS - 2) * NLD>();
       issue(ab, bb, L, live ? 64 * (i + p + NS - 1) : 64 * min(i + p + NS - 1, nst - 1), live || i + p + NS - 1 < nst,
             st[(p + NS - 1) % NS]);
-      Frags f;
-      read(st[p], L, f);
-      if (edge) mask(f, 64 * (s0 + i + p), q, limit);
-      multiply(f, acc);
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        Frags f;
+        read(st[p], L, ks, f);
+        if (edge) mask(f, 64 * (s0 + i + p) + 32 * ks, q, limit);
+        multiply(f, acc);
+      }
     };
     auto edge = [&](int end) {
       for (; i < end; i += NS) {
