@@ -35,6 +35,13 @@
 // with d <= i contribute exactly 0 (their dz is an exact 0), so the diagonal blocks need no mask.  Workgroups are numbered block-major: the ones that run together
 // on an XCD share their flip block and so stream the same rows of the second layer through that
 // XCD's L2, and the longest sweeps (the first blocks) start first.
+//
+// What bounds it: VALU issue (8 instructions and one exponential per element, about two thirds of the cycles at
+// n = 1000, h = 239, B = 512) with the products beneath.  Flip kernel there, BF16: 371 us with a row of dR per pass of
+// a wave (half its lanes idle at h = 239, a wait for c[i] and s_i and a branch per rounding on each row) and two
+// waves per SIMD, 248 us with the rows dealt four lanes each and v_cvt_pk_bf16_f32, 244 us without the blocks before
+// the first flipped site, 236 us with the first B fragments in flight while dR is built, 201 us with one set of A
+// fragments (two sets spilled at three waves per SIMD, and the spill waited for the next block's loads).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -108,11 +115,19 @@ __device__ inline uint4 tim_ld16(tim_rsrc_t r, uint32_t voff, uint32_t soff) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0));
 }
 
+// two floats to BF16, to nearest even, the first in the low half (v_cvt_pk_bf16_f32)
+__device__ inline uint32_t tim_pack_bf16(float a, float b) {
+  typedef __attribute__((ext_vector_type(2))) float f2_t;
+  typedef __attribute__((ext_vector_type(2))) __bf16 b2_t;
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f2_t){a, b}, b2_t));
+}
+
 // dR rows of the flip block, the per-lane running sums, and the final reduction are shared by
 // both sweeps below; NF > 0 selects the pipelined BF16 sweep (register-prefetched operands),
 // NF = 0 the plain one (FP32 weights, or K ranges too long to prefetch).
+// Waves per SIMD: three fit at NF = 8 (155 registers; four spill: 349 us against 201), two at NF = 16 (219).
 template <typename T, int NF>
-__global__ __launch_bounds__(256) void tim_flip_kernel(
+__global__ __launch_bounds__(256, NF == 8 ? 3 : 2) void tim_flip_kernel(
     const int8_t* __restrict__ S, int64_t lds, const float* __restrict__ A, int64_t ldh,
     const float* __restrict__ Z, int64_t ldz, const T* __restrict__ P, const T* __restrict__ P2,
     const int32_t* __restrict__ c, int n, int h, int64_t B, int nbi, const float* __restrict__ alpha,
@@ -139,52 +154,79 @@ __global__ __launch_bounds__(256) void tim_flip_kernel(
   const int kbase = (c[i0] / KS) * KS;
   const int kw = kwmax - kbase;
 
-  for (int k = t; k < kwmax; k += 256) a_s[k] = k < h ? A[b * ldh + k] : 0.f;
-  __syncthreads();
-  // dR rows of the block: wave wv builds rows wv + 4 j (j < 16).  A lane covers CPL consecutive
-  // columns (16 bytes of weights) per pass; the 16 rows' weights are fetched together (buffer
-  // loads: columns past the block's K range and rows past n read zeros), then dR goes to LDS in
-  // 16-byte stores.
+  auto build_rows = [&](auto&& between) {
+  // dR rows of the block: thread t builds row t >> 2, the columns CPL (t & 3) + 4 CPL j (16 bytes of
+  // weights each; rows past n read zeros).  A row's first unit and spin are then read once, no lane is
+  // idle whatever the K range, and the weights of JP column groups are in flight together.
   {
-    constexpr int CPL = 16 / (int)sizeof(T);
+    constexpr int CPL = 16 / (int)sizeof(T), JP = 8;
     const tim_rsrc_t rp = tim_rsrc(P, (uint32_t)((int64_t)n * ldh * sizeof(T)));
-    for (int c0 = 0; c0 < kw; c0 += 64 * CPL) {
-      const int kk = c0 + CPL * lane;                  // first column of the lane (relative to kbase)
-      const bool col_ok = kk < kw;
-      uint4 pv[16];
+    const int r = t >> 2, i = i0 + r;
+    const int col = CPL * (t & 3);                     // relative to kbase, as kk below
+    const uint32_t off = i < n ? (uint32_t)(((int64_t)i * ldh + kbase + col) * sizeof(T)) : TIM_OOB;
+    const int nj = (kw + 4 * CPL - 1) / (4 * CPL);
+    uint4 pv[JP];
+    auto fetch = [&](int j0) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int i = i0 + wv + 4 * j;
-        const uint32_t off = (uint32_t)(((int64_t)i * ldh + kbase + kk) * sizeof(T));
-        pv[j] = tim_ld16(rp, (col_ok && i < n) ? off : TIM_OOB, 0);
-      }
-      if (col_ok) {
-        float av[CPL];
+      for (int jj = 0; jj < JP; ++jj)
+        pv[jj] = tim_ld16(rp, col + 4 * CPL * (j0 + jj) < kw ? off : TIM_OOB, (uint32_t)(64 * (j0 + jj)));
+    };
+    fetch(0);
+    between();
+    const int ci = i < n ? c[i] : h;                   // rows past n: no unit receives them
+    const float two_s = i < n ? 2.f * (float)Sb[i] : 0.f;
+    const int cfull = i0 + TIM_BM <= n ? c[i0 + TIM_BM - 1] : h;  // every unit from here to h receives every row's site
+    for (int k = t; k < kwmax; k += 256) a_s[k] = k < h ? A[b * ldh + k] : 0.f;
+    __syncthreads();
+    auto build = [&](const uint4& pw, int kk, bool masked) {
+      union {
+        uint4 u;
+        T e[CPL];
+      } w;
+      w.u = pw;
+      union {
+        float4 q[CPL / 4];
+        float e[CPL];
+      } av;
 #pragma unroll
-        for (int e = 0; e < CPL; ++e) av[e] = a_s[kbase + kk + e];
+      for (int e = 0; e < CPL / 4; ++e) av.q[e] = *(const float4*)(a_s + kbase + kk + 4 * e);
+      float v[CPL];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int r = wv + 4 * j, i = i0 + r;
-          const int ci = i < n ? c[i] : h;             // rows past n: no unit receives them
-          const float two_s = i < n ? 2.f * (float)Sb[i] : 0.f;
-          union {
-            uint4 u;
-            T e[CPL];
-          } w, o;
-          w.u = pv[j];
-#pragma unroll
-          for (int e = 0; e < CPL; ++e) {
-            const int k = kbase + kk + e;
-            const float v = fmaxf(av[e] - two_s * to_f32<T>(w.e[e]), 0.f) - fmaxf(av[e], 0.f);
-            o.e[e] = from_f32<T>((k >= ci && k < h) ? v : 0.f);
-          }
-          *(uint4*)(dR + (size_t)r * ldr + kk) = o.u;
+      for (int e = 0; e < CPL; ++e) {
+        v[e] = fmaxf(av.e[e] - two_s * to_f32<T>(w.e[e]), 0.f) - fmaxf(av.e[e], 0.f);
+        if (masked) {
+          const int k = kbase + kk + e;
+          v[e] = (k >= ci && k < h) ? v[e] : 0.f;
         }
       }
+      T* dst = dR + (size_t)r * ldr + kk;
+      if constexpr (sizeof(T) == 2) {
+        uint32_t o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = tim_pack_bf16(v[2 * e], v[2 * e + 1]);
+        *(uint4*)dst = make_uint4(o[0], o[1], o[2], o[3]);
+      } else {
+        *(float4*)dst = make_float4(v[0], v[1], v[2], v[3]);
+      }
+    };
+    for (int j0 = 0;;) {
+#pragma unroll
+      for (int jj = 0; jj < JP; ++jj) {
+        const int k0 = 4 * CPL * (j0 + jj);            // wave-uniform
+        if (k0 < kw && col + k0 < kw) {
+          if (kbase + k0 >= cfull && kbase + k0 + 4 * CPL <= h)
+            build(pv[jj], col + k0, false);
+          else
+            build(pv[jj], col + k0, true);
+        }
+      }
+      if ((j0 += JP) >= nj) break;
+      fetch(j0);
     }
   }
   __syncthreads();
 
+  };
   // per lane: rows 16 mi + 4 (lane >> 4) + r of the block, for the lane's column of each site block
   float lin[4][4], prod[4][4];
 #pragma unroll
@@ -221,8 +263,9 @@ __global__ __launch_bounds__(256) void tim_flip_kernel(
       if (dw >= n) return kbase;
       return min((int)round_up(c[min(dw + 31, n - 1)], 32), kwmax);
     };
-    // the sweep starts at the site block holding the first flipped site (sites d <= i add 0)
-    const int qd0 = i0 / TIM_BN;
+    // the sweep starts at the site block holding the first flipped site, or one later where all of the wave's
+    // columns lie before that site (sites d <= i add 0)
+    const int qd0 = i0 / TIM_BN + (i0 / TIM_BN * TIM_BN + 32 * wv + 31 < i0 ? 1 : 0);
     uint4 bfr[2][NF];  // the two column groups' B fragments
     int nk = (kend(qd0) - kbase) / 32;
     int dl[2], s_raw[2];
@@ -251,7 +294,7 @@ __global__ __launch_bounds__(256) void tim_flip_kernel(
         }
       }
     };
-    fetch_b(nk);
+    build_rows([&]() { fetch_b(nk); });
     for (int qd = qd0;; ++qd) {
       const int dw = qd * TIM_BN + 32 * wv;
       if (dw >= n) break;
@@ -264,28 +307,24 @@ __global__ __launch_bounds__(256) void tim_flip_kernel(
           for (int mi = 0; mi < 4; ++mi) acc[g][mi] = (floatx4_t){0.f, 0.f, 0.f, 0.f};
       } else {
         constexpr int LDR = tim_ldr<bf16_t>(32 * NF);   // == ldr: every LDS offset below is an immediate
-        uint4 a[2][4];
+        uint4 a[4];
 #pragma unroll
-        for (int mi = 0; mi < 4; ++mi) a[0][mi] = *(const uint4*)(arow + 16 * mi * LDR);
-        // a guarded body rather than an early exit, so that the loop unrolls fully; the next
-        // step's A fragments are read whether or not it is needed (within the row; unused)
+        for (int mi = 0; mi < 4; ++mi) a[mi] = *(const uint4*)(arow + 16 * mi * LDR);
+        // a guarded body rather than an early exit, so that the loop unrolls fully.  An A fragment serves
+        // both column groups (half the LDS reads per product) and is replaced by the next step's right
+        // after, needed or not (within the row): a second set would not fit beside the B fragments
+        // with three waves per SIMD.
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
           if (f < nk) {
-            if (f + 1 < NF) {
 #pragma unroll
-              for (int mi = 0; mi < 4; ++mi)
-                a[(f + 1) & 1][mi] = *(const uint4*)(arow + 16 * mi * LDR + 32 * (f + 1));
-            }
-            // each A fragment serves both column groups: half the LDS reads per product
+            for (int mi = 0; mi < 4; ++mi) {
 #pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              const bf16x8_t bf = __builtin_bit_cast(bf16x8_t, bfr[g][f]);
-#pragma unroll
-              for (int mi = 0; mi < 4; ++mi)
+              for (int g = 0; g < 2; ++g)
                 acc[g][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8_t, a[f & 1][mi]), bf,
+                    __builtin_bit_cast(bf16x8_t, a[mi]), __builtin_bit_cast(bf16x8_t, bfr[g][f]),
                     f == 0 ? (floatx4_t){0.f, 0.f, 0.f, 0.f} : acc[g][mi], 0, 0, 0);
+              if (f + 1 < NF) a[mi] = *(const uint4*)(arow + 16 * mi * LDR + 32 * (f + 1));
             }
           }
         }
@@ -309,6 +348,7 @@ __global__ __launch_bounds__(256) void tim_flip_kernel(
       nk = nk_next;
     }
   } else {
+    build_rows([]() {});
     for (int qd = i0 / TIM_BN; qd < nbd; ++qd) {
       const int dw0 = qd * TIM_BN + 32 * wv;   // first column of this wave
       if (dw0 >= n) break;                      // wave-uniform: nothing left for this wave
@@ -365,15 +405,23 @@ __global__ __launch_bounds__(256) void tim_flip_kernel(
       v += VQMC_DPP(v, 0x140);  // row_mirror: every lane of the DPP row holds the row sum
       if (gcol == 0) red[wv * TIM_BM + 16 * mi + 4 * grow + r] = v;
     }
+  // the last step's operands, read before the barrier
+  const int it = i0 + t;
+  const bool row_ok = t < TIM_BM && it < n;
+  float si = 0.f, zi = 0.f, al = 0.f, be = 0.f;
+  if (row_ok) {
+    si = (float)Sb[it];
+    zi = Zb[it];
+    al = alpha[it];
+    be = beta[it];
+  }
   __syncthreads();
   if (t < TIM_BM) {
-    const int i = i0 + t;
     double cterm = 0.0;
-    if (i < n) {
-      const float si = (float)Sb[i];
-      const float Di = ((red[t] + red[TIM_BM + t]) + (red[2 * TIM_BM + t] + red[3 * TIM_BM + t])) - si * Zb[i];
-      if (Dout) Dout[b * ldd + i] = Di;
-      cterm = (double)alpha[i] * exp(0.5 * (double)Di) + (double)beta[i] * (double)si;
+    if (row_ok) {
+      const float Di = ((red[t] + red[TIM_BM + t]) + (red[2 * TIM_BM + t] + red[3 * TIM_BM + t])) - si * zi;
+      if (Dout) Dout[b * ldd + it] = Di;
+      cterm = (double)al * exp(0.5 * (double)Di) + (double)be * (double)si;
     }
     contrib[t] = cterm;
   }
