@@ -18,12 +18,7 @@ __host__ __device__ inline int64_t round_up(int64_t x, int64_t m) { return (x + 
 
 // ---------------------------------------------------------------- bfloat16
 // float32 -> bfloat16, round to nearest even (NaN stays a quiet NaN).
-__device__ inline bf16_t f32_to_bf16(float x) {
-  uint32_t b = __float_as_uint(x);
-  if ((b & 0x7F800000u) == 0x7F800000u && (b & 0x007FFFFFu)) return (bf16_t)((b >> 16) | 0x0040u);
-  b += 0x7FFFu + ((b >> 16) & 1u);
-  return (bf16_t)(b >> 16);
-}
+__device__ inline bf16_t f32_to_bf16(float x) { return __builtin_bit_cast(bf16_t, (__bf16)x); }
 __device__ inline float bf16_to_f32(bf16_t x) { return __uint_as_float(((uint32_t)x) << 16); }
 
 template <typename T> __device__ inline float to_f32(T x);
