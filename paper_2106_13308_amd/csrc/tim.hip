@@ -41,7 +41,8 @@
 // a wave (half its lanes idle at h = 239, a wait for c[i] and s_i and a branch per rounding on each row) and two
 // waves per SIMD, 248 us with the rows dealt four lanes each and v_cvt_pk_bf16_f32, 244 us without the blocks before
 // the first flipped site, 236 us with the first B fragments in flight while dR is built, 201 us with one set of A
-// fragments (two sets spilled at three waves per SIMD, and the spill waited for the next block's loads).
+// fragments (two sets spilled at three waves per SIMD, and the spill waited for the next block's loads), 179 us with a
+// ring of four K steps of B fragments (four waves per SIMD; at n = 10000, h = 424, B = 256 the step 9.06 -> 8.78 ms).
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -123,11 +124,11 @@ __device__ inline uint32_t tim_pack_bf16(float a, float b) {
 }
 
 // dR rows of the flip block, the per-lane running sums, and the final reduction are shared by
-// both sweeps below; NF > 0 selects the pipelined BF16 sweep (register-prefetched operands),
-// NF = 0 the plain one (FP32 weights, or K ranges too long to prefetch).
-// Waves per SIMD: three fit at NF = 8 (155 registers; four spill: 349 us against 201), two at NF = 16 (219).
+// both sweeps below; NF > 0 selects the pipelined BF16 sweep (register-prefetched operands, K ranges up
+// to 32 NF), NF = 0 the plain one (FP32 weights, or longer K ranges).
+// Waves per SIMD: four at NF = 8; the LDS rows of NF = 16 leave room for two.
 template <typename T, int NF>
-__global__ __launch_bounds__(256, NF == 8 ? 3 : 2) void tim_flip_kernel(
+__global__ __launch_bounds__(256, NF == 8 ? 4 : 2) void tim_flip_kernel(
     const int8_t* __restrict__ S, int64_t lds, const float* __restrict__ A, int64_t ldh,
     const float* __restrict__ Z, int64_t ldz, const T* __restrict__ P, const T* __restrict__ P2,
     const int32_t* __restrict__ c, int n, int h, int64_t B, int nbi, const float* __restrict__ alpha,
@@ -266,7 +267,11 @@ __global__ __launch_bounds__(256, NF == 8 ? 3 : 2) void tim_flip_kernel(
     // the sweep starts at the site block holding the first flipped site, or one later where all of the wave's
     // columns lie before that site (sites d <= i add 0)
     const int qd0 = i0 / TIM_BN + (i0 / TIM_BN * TIM_BN + 32 * wv + 31 < i0 ? 1 : 0);
-    uint4 bfr[2][NF];  // the two column groups' B fragments
+    // The two column groups' B fragments, a ring of NR K steps: the first NR are fetched a block ahead, a later step
+    // when its slot's products are issued.  Most blocks need no more (h / 3 units on average), and 125 registers let
+    // four waves share a SIMD (all steps held: 155 and three waves, 201 us against 179; h = 424: 2 % slower)
+    constexpr int NR = 4;
+    uint4 bfr[2][NR];
     int nk = (kend(qd0) - kbase) / 32;
     int dl[2], s_raw[2];
     float z_raw[2];
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(256, NF == 8 ? 3 : 2) void tim_flip_kernel(
     // through the address unit, so only the last group of a block carries any
     auto fetch_b = [&](int need) {
 #pragma unroll
-      for (int g4 = 0; g4 < NF / 4; ++g4) {
+      for (int g4 = 0; g4 < NR / 4; ++g4) {
         if (4 * g4 < need) {
 #pragma unroll
           for (int f = 4 * g4; f < 4 * g4 + 4; ++f)
@@ -312,8 +317,7 @@ __global__ __launch_bounds__(256, NF == 8 ? 3 : 2) void tim_flip_kernel(
         for (int mi = 0; mi < 4; ++mi) a[mi] = *(const uint4*)(arow + 16 * mi * LDR);
         // a guarded body rather than an early exit, so that the loop unrolls fully.  An A fragment serves
         // both column groups (half the LDS reads per product) and is replaced by the next step's right
-        // after, needed or not (within the row): a second set would not fit beside the B fragments
-        // with three waves per SIMD.
+        // after, needed or not (within the row): a second set would cost a wave per SIMD.
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
           if (f < nk) {
@@ -322,9 +326,13 @@ __global__ __launch_bounds__(256, NF == 8 ? 3 : 2) void tim_flip_kernel(
 #pragma unroll
               for (int g = 0; g < 2; ++g)
                 acc[g][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                    __builtin_bit_cast(bf16x8_t, a[mi]), __builtin_bit_cast(bf16x8_t, bfr[g][f]),
+                    __builtin_bit_cast(bf16x8_t, a[mi]), __builtin_bit_cast(bf16x8_t, bfr[g][f % NR]),
                     f == 0 ? (floatx4_t){0.f, 0.f, 0.f, 0.f} : acc[g][mi], 0, 0, 0);
               if (f + 1 < NF) a[mi] = *(const uint4*)(arow + 16 * mi * LDR + 32 * (f + 1));
+            }
+            if (f + NR < NF && f + NR < nk) {
+#pragma unroll
+              for (int g = 0; g < 2; ++g) bfr[g][f % NR] = tim_ld16(rs, roff[g], 64u * (f + NR));
             }
           }
         }
@@ -499,7 +507,7 @@ static hipError_t tim_energy_t(const vqmc_made& m, const vqmc_tim& H, const int8
   const int64_t np2 = (int64_t)n * ldh;
   tim_w2_kernel<T><<<(unsigned)((np2 + 255) / 256), 256, 0, st>>>((const T*)m.P, m.c, n, ldh, P2);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  // the pipelined sweep holds NF K steps of B fragments in registers: K ranges up to 32 NF
+  // the pipelined sweep is unrolled over NF K steps, its LDS row stride a constant: K ranges up to 32 NF
   auto kern = tim_flip_kernel<T, 0>;
   int kalloc = (int)round_up(h, TimK<T>::KS);
   if constexpr (sizeof(T) == 2) {
