@@ -31,6 +31,7 @@
 // batch-contiguous (X[j][b], ld(B) columns) and reach the tile through LDS panels of rows.  A combine pass adds the items' partial sums in a fixed
 // order and mirrors the upper tiles.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -384,37 +385,53 @@ __global__ __launch_bounds__(256) void sr_seg_pack_tile_kernel(const bf16_t* __r
 // ring of GM_RING register sets (loaded GM_RING chunks ahead); the units' R and D rows come
 // through LDS panels of GM_PR units.  Workgroups are dealt round-robin to the 8 XCDs; each
 // XCD takes a contiguous run of the tile order, so that its tiles share row tiles in its L2.
-constexpr int GM_PR = 64;
-constexpr int GM_RING = 4;
+//
+// What bounds it: the latency of the chunk loads and of the unit loop, 448 us for one tile on a CU and 527 us for two at
+// n = 10000, h = 1000, so 528 tiles (B = 2048) on the 512 slots of two per CU took 954 us: sixteen tiles ran a second
+// round alone.  QUARTERS is the form for such a short last round: the remaining tiles run as single waves, one 32 x 32
+// quadrant each (the other three waves of the workgroup end at once), numbered first so that they spread over the CUs,
+// and a ring of two chunks, panels of 32 units and 32-bit row offsets let them fit beside two whole tiles (168
+// registers, 32 KB): 640 us (B = 4096, 2080 tiles: 2670 -> 2460).  A quadrant's sums keep their order.
+constexpr int GM_SLOTS = 512;  // two workgroups on each of 256 CUs
 struct GmFrag {
   uint2 ga[2], gb[2], sa[2], sb[2];
   int32_t info;  // the chunk's descriptor (same in every lane)
 };
 typedef __attribute__((ext_vector_type(4))) short gm_bf16x4_t;
 
-__global__ __launch_bounds__(256) void sr_gram_mfma_kernel(const bf16_t* __restrict__ Gs, const bf16_t* __restrict__ Ss,
+template <int GM_RING, int GM_PR, bool QUARTERS>
+__global__ __launch_bounds__(256, QUARTERS ? 3 : 2) void sr_gram_mfma_kernel(const bf16_t* __restrict__ Gs, const bf16_t* __restrict__ Ss,
                                                            int64_t ldk, const bf16_t* __restrict__ Rt,
                                                            const bf16_t* __restrict__ Dt, int64_t ldb,
                                                            const int32_t* __restrict__ cinfo,
                                                            const int32_t* __restrict__ seg_choff,
                                                            const int32_t* __restrict__ tab, int h, int64_t B, int nt,
-                                                           float* __restrict__ K) {
+                                                           int whole, float* __restrict__ K) {
   __shared__ __align__(16) float pr[GM_PR][2 * GR_T];
   __shared__ __align__(16) float pd[GM_PR][2 * GR_T];
   int ti, tj;
-  {
-    const int w = blockIdx.x, G = gridDim.x, x = w & 7, q = G >> 3, r = G & 7;
+  const int t = threadIdx.x, lane = t & 63;
+  const int nq = gridDim.x - whole;  // quarters come first
+  const bool quarter = QUARTERS && (int)blockIdx.x < nq;
+  int wv = t >> 6;
+  if (quarter) {
+    const int w = blockIdx.x;
+    upper_tile(whole + (w >> 2), nt, ti, tj);
+    wv = w & 3;
+    if (t >= 64 || (ti == tj && wv == 2)) return;
+  } else {
+    const int w = blockIdx.x - nq, G = whole, x = w & 7, q = G >> 3, r = G & 7;
     upper_tile(x * q + min(x, r) + (w >> 3), nt, ti, tj);
   }
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;
   const int64_t b0 = (int64_t)ti * GR_T, b1 = (int64_t)tj * GR_T;
-  int64_t ra[2], rb[2];  // fragment rows, clamped (results of rows >= B are never stored)
+  // byte offsets of the fragment rows in a chunk, clamped (results of rows >= B are never stored)
+  typename std::conditional<QUARTERS, uint32_t, int64_t>::type ra[2], rb[2];
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
-    ra[i] = min(b0 + wm + 16 * i + lr, B - 1) * SG_C + 4 * lg;
-    rb[i] = min(b1 + wn + 16 * i + lr, B - 1) * SG_C + 4 * lg;
+    ra[i] = (min(b0 + wm + 16 * i + lr, B - 1) * SG_C + 4 * lg) * 2;
+    rb[i] = (min(b1 + wn + 16 * i + lr, B - 1) * SG_C + 4 * lg) * 2;
   }
   floatx4_t acc[2][2], F[2][2], F2[2][2], X[2][2];
 #pragma unroll
@@ -433,14 +450,15 @@ __global__ __launch_bounds__(256) void sr_gram_mfma_kernel(const bf16_t* __restr
 
   auto load = [&](GmFrag& f, int q) {
     const int qc = min(q, max(nch - 1, 0));
-    const int64_t ko = (int64_t)qc * B * SG_C;
+    const char* gq = (const char*)(Gs + (int64_t)qc * B * SG_C);
+    const char* sq = (const char*)(Ss + (int64_t)qc * B * SG_C);
     f.info = cinfo[qc];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      f.ga[i] = *(const uint2*)(Gs + ra[i] + ko);
-      f.gb[i] = *(const uint2*)(Gs + rb[i] + ko);
-      f.sa[i] = *(const uint2*)(Ss + ra[i] + ko);
-      f.sb[i] = *(const uint2*)(Ss + rb[i] + ko);
+      f.ga[i] = *(const uint2*)(gq + ra[i]);
+      f.gb[i] = *(const uint2*)(gq + rb[i]);
+      f.sa[i] = *(const uint2*)(sq + ra[i]);
+      f.sb[i] = *(const uint2*)(sq + rb[i]);
     }
   };
   // unit u: F += RR'_u, acc += DD'_u (.) F2 (F2 holds the segments with gamma <= u)
@@ -448,9 +466,11 @@ __global__ __launch_bounds__(256) void sr_gram_mfma_kernel(const bf16_t* __restr
     for (; unit < uend; ++unit) {
       if (unit >= pbase + GM_PR) {
         __syncthreads();
+        const int seg8 = t & 7;  // 8 threads per row, 16 samples each
+        const int npass = QUARTERS && quarter ? GM_PR / 8 : GM_PR / 32;  // of 64 or 256 threads
 #pragma unroll
-        for (int half = 0; half < GM_PR / 32; ++half) {
-          const int r = 32 * half + (t >> 3), seg8 = t & 7;  // 8 threads per row, 16 samples each
+        for (int pass = 0; pass < npass; ++pass) {
+          const int r = (QUARTERS && quarter ? 8 : 32) * pass + (t >> 3);
           if (unit + r < h) {
             const int64_t col = (seg8 < 4 ? b0 : b1) + 16 * (seg8 & 3);
 #pragma unroll
@@ -608,8 +628,16 @@ static hipError_t launch_sr_gram_mfma(const bf16_t* G, const int8_t* S, int64_t 
   sr_seg_pack_tile_kernel<<<pgrid, 256, 0, st>>>(G, S, ldn, inv, choff, tab, B, Gs, Ss);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int nt = (int)((B + GR_T - 1) / GR_T);
-  const int64_t pairs = (int64_t)nt * (nt + 1) / 2;
-  sr_gram_mfma_kernel<<<(unsigned)pairs, 256, 0, st>>>(Gs, Ss, L.ldk, Rt, Dt, ldb, cinfo, choff, tab, h, B, nt, K);
+  const int pairs = (int)((int64_t)nt * (nt + 1) / 2);
+  // tiles past the last full round; up to 64 of them are 256 quadrants, the third slot of each CU (more
+  // would share CUs with each other: the plain form again)
+  const int rest = pairs % GM_SLOTS;
+  if (pairs > GM_SLOTS && rest > 0 && rest <= GM_SLOTS / 8)
+    sr_gram_mfma_kernel<2, 32, true><<<(unsigned)(pairs + 3 * rest), 256, 0, st>>>(
+        Gs, Ss, L.ldk, Rt, Dt, ldb, cinfo, choff, tab, h, B, nt, pairs - rest, K);
+  else
+    sr_gram_mfma_kernel<4, 64, false><<<(unsigned)pairs, 256, 0, st>>>(Gs, Ss, L.ldk, Rt, Dt, ldb, cinfo, choff, tab,
+                                                                       h, B, nt, pairs, K);
   return hipGetLastError();
 }
 
