@@ -267,7 +267,8 @@ int vqmc_sample_plain(const vqmc_made* m, int64_t B, uint64_t seed, uint64_t ste
                       size_t ws_bytes, void* stream);
 
 /* Local energy of a diagonal Hamiltonian (Sec. 2.1 local energy = H_xx).  E is int64
- * for CSR_INT (exact), double otherwise (FP64 accumulation of exact products).
+ * for CSR_INT (exact), double otherwise: exact products summed in FP64, or (dense rows whose entries are
+ * all multiples of 2^-54 of the power of two above the largest) summed exactly and then rounded to FP64.
  * S: B x ld(n) int8 spins (+1/-1; columns >= n are ignored), 16-byte aligned, else EINVAL.
  * The dense kind needs vqmc_energy_workspace_bytes() of workspace (CSR kinds need none;
  * ws may then be NULL). */

@@ -298,15 +298,16 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bytes_kernel(int n, int
   }
 }
 
-// ---------------------------------------------------------------- dense J (fixed point)
+// ---------------------------------------------------------------- dense J
 // E_b = sum_i s_bi y_bi with y_bi = sum_{j>i} J_ij s_bj (strict upper triangle only).
 //
 // The spins are integers, so y is a contraction of integers once row i of J is written in fixed
-// point: with 2^e_i above the row's largest entry, J_ij = 2^(e_i - 54) q_ij and |q_ij| < 2^54, exact for
-// entries down to 2^-31 of the largest and rounded to 2^-55 of it below, where a double-precision
-// sum rounds its partial sums to 2^-53.  q is split into seven signed bytes, each plane is
+// point: with 2^e_i above the row's largest entry, J_ij = 2^(e_i - 54) q_ij and |q_ij| < 2^54.  A row is taken this
+// way if that is exact for every entry: no bit of a non-zero entry below 2^(e_i - 54) (so any row whose entries lie
+// within 2^30 of each other).  q is split into seven signed bytes, each plane is
 // multiplied with the spins on the int8 matrix cores (exact 32-bit sums: 128 n < 2^31), and the
-// seven sums of a row are joined by six double-precision multiply-adds.
+// seven sums of a row are joined by six double-precision multiply-adds, the only roundings.  A tile with a row of
+// another kind (entries further apart, NaN, infinities) is summed by the FP64 matrix cores, every entry a double.
 //
 // Tile: 16 IB rows x 32 samples per wave, NW waves with the same rows, 64 columns of J per step.  The
 // workgroup turns each step's FP32 entries into byte planes in LDS itself (13 instructions an entry
@@ -316,37 +317,50 @@ __global__ __launch_bounds__(EB_THREADS) void energy_csr_bytes_kernel(int n, int
 //
 // A step's products run beside the conversion of the next step, one barrier per step.
 //
-// n = 2000, B = 8192: 158 us (1.45 POPS of the 4.6 that a loop of these products reaches) and 12 us
-// for the exponents and the sum of the tiles' partials; the FP64 matrix cores took 1172 us at 0.35 of
-// their peak.  n = 1000, B = 512: 14 + 10 us, 65 before.  Copies without the conversion take 133 us,
-// without the spin loads 150, with 12 of the 28 products of a step 106: what is left is each
-// workgroup's start and end, one workgroup per CU.  Against 64-bit sums of the N(0, 1/n) couplings the
-// energies are off by 1.3e-16 of their norm, as before.
+// n = 2000, B = 8192: 154 us, of which 12 for the exponents and the sum of the tiles' partials (the products run at
+// 1.45 POPS of the 4.6 that a loop of them reaches); n = 1000, B = 512: 24 us.  Copies without the conversion take
+// 133 us, without the spin loads 150, with 12 of the 28 products of a step 106: what is left is each workgroup's start
+// and end, one workgroup per CU.  With every row in FP64, as before, 1188 us and 65; through this kernel's FP64 tiles,
+// a matrix of such rows alone, 1155 and 50.  Against 64-bit sums of the N(0, 1/n) couplings the energies are off by
+// 1.3e-16 of their norm, as before.
 constexpr int DK = 64;  // columns of J per step
 constexpr int DD = 7;            // byte planes
-constexpr int DNONFINITE = INT32_MIN;
-typedef __attribute__((ext_vector_type(4))) int32_t i32x4_t;
+constexpr int DWIDE = INT32_MIN;
 struct __attribute__((aligned(8))) Bytes16 {  // spin rows may start on any 8-byte boundary
   uint32_t x[4];
 };
+typedef __attribute__((ext_vector_type(4))) int32_t i32x4_t;
 
-// ex[i] = e with |J_ij| < 2^e for every j > i, DNONFINITE if the row has a NaN or infinity; a wave a row.
+// ex[i] = e with |J_ij| < 2^e for every j > i, DWIDE if 2^(e - 54) does not divide every entry of the row or it has a
+// NaN or infinity; a wave a row.
 __global__ __launch_bounds__(256) void energy_rowmax_kernel(int n, const float* __restrict__ J, int32_t* __restrict__ ex) {
   const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (i >= n) return;
   const float* row = J + (int64_t)i * n;
   uint32_t m = 0;
+  int low = INT32_MAX;  // the lowest bit set in an entry, as the exponent field of 2^23 times it
+  auto take = [&](uint32_t v) {
+    m = max(m, v);
+    const uint32_t f = v >> 23, sig = (v & 0x7FFFFFu) | (f ? 0x800000u : 0u);
+    if (sig) low = min(low, (int)max(f, 1u) + __builtin_ctz(sig));
+  };
   int j = i + 1 + lane;
   for (; j + 192 < n; j += 256) {
     uint32_t v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = __float_as_uint(row[j + 64 * u]) & 0x7FFFFFFFu;
-    m = max(max(m, max(v[0], v[1])), max(v[2], v[3]));
-  }
-  for (; j < n; j += 64) m = max(m, __float_as_uint(row[j]) & 0x7FFFFFFFu);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
-  if (lane == 0) ex[i] = m >= 0x7F800000u ? DNONFINITE : max((int)(m >> 23), 1) - 126;
+    for (int u = 0; u < 4; ++u) take(v[u]);
+  }
+  for (; j < n; j += 64) take(__float_as_uint(row[j]) & 0x7FFFFFFFu);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    m = max(m, (uint32_t)__shfl_xor((int)m, o));
+    low = min(low, __shfl_xor(low, o));
+  }
+  const int f = max((int)(m >> 23), 1);
+  // e = f - 126; a bit of exponent field low weighs 2^(low - 150)
+  if (lane == 0) ex[i] = m >= 0x7F800000u || low < f - 30 ? DWIDE : f - 126;
 }
 
 // q of one entry as eight bytes, the low seven of them the signed digits
@@ -359,6 +373,84 @@ __device__ inline uint2 fixed_digits(float v, int e) {
   constexpr uint64_t bias = 0x0080808080808080ull;
   const uint64_t q = ((uint64_t)((int64_t)hi * 2147483648ll) + (uint64_t)lo + bias) ^ bias;
   return make_uint2((uint32_t)q, (uint32_t)(q >> 32));
+}
+
+// Sums over 16 IB rows from i0 and the wave's 32 samples (rows srow of S, clamped) by v_mfma_f64_16x16x4, the columns
+// in rising order: y[ib][sb][e] belongs to row i0 + 16 ib + 4 e + lane / 16 and sample 16 sb + lane % 16.  Operands
+// straight from memory, the next sixteen columns' loads in flight: a product takes 64 cycles, so the matrix
+// cores bound it (a tile's J entries serve 32 samples a load).
+template <int IB>
+__device__ inline void dense_rows_f64(int n, const float* __restrict__ J, int i0, const int8_t* const (&srow)[2],
+                                      doublex4_t (&y)[IB][2]) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) y[ib][sb] = (doublex4_t){0.0, 0.0, 0.0, 0.0};
+  float jv[2][IB][4];
+  uint4 sv[2][2];
+  auto fetch = [&](int j0, const int q) {
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib) {
+      const float* row = J + (int64_t)min(i0 + 16 * ib + r, n - 1) * n;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) jv[q][ib][kk] = row[min(j0 + 4 * kk + g, n - 1)];
+    }
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) sv[q][sb] = *(const uint4*)(srow[sb] + j0);
+  };
+  const int jlast = (n - 1) / 16 * 16;  // past the end: the last columns' loads again, never used
+  auto step = [&](int j0, const int q) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      const int j = j0 + 4 * kk + g;
+      double a[IB], s[2];
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib) {
+        const int i = i0 + 16 * ib + r;
+        a[ib] = i < n && j < n && j > i ? (double)jv[q][ib][kk] : 0.0;
+      }
+#pragma unroll
+      for (int sb = 0; sb < 2; ++sb) {
+        const uint32_t w = kk == 0 ? sv[q][sb].x : kk == 1 ? sv[q][sb].y : kk == 2 ? sv[q][sb].z : sv[q][sb].w;
+        s[sb] = j < n ? (double)(int8_t)(w >> (8 * g)) : 0.0;
+      }
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+        for (int sb = 0; sb < 2; ++sb) y[ib][sb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[ib], s[sb], y[ib][sb], 0, 0, 0);
+    }
+  };
+  int j0 = i0 / 16 * 16;
+  fetch(j0, 0);
+  for (; j0 < n; j0 += 32) {
+    fetch(min(j0 + 16, jlast), 1);
+    step(j0, 0);
+    fetch(min(j0 + 32, jlast), 0);
+    if (j0 + 16 < n) step(j0 + 16, 1);
+  }
+}
+
+// sum_i s_bi y_bi of dense_rows_f64's rows, stored by the lanes of the first group
+template <int IB>
+__device__ inline void dense_store_f64(int n, int i0, const int8_t* const (&srow)[2], const doublex4_t (&y)[IB][2],
+                                       int64_t b0, int64_t B, double* __restrict__ part) {
+  const int lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int sb = 0; sb < 2; ++sb) {
+    double v = 0.0;
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int i = i0 + 16 * ib + 4 * e + g;
+        if (i < n) v += (double)srow[sb][i] * y[ib][sb][e];
+      }
+    v += __shfl_xor(v, 16);
+    v += __shfl_xor(v, 32);
+    const int64_t b = b0 + 16 * sb + r;
+    if (g == 0 && b < B) part[b] = v;
+  }
 }
 
 // VEC: rows of J start 16-byte aligned (n a multiple of four and J 16-byte aligned)
@@ -376,9 +468,20 @@ __global__ __launch_bounds__(64 * NW, 2) void energy_dense_kernel(int n, int64_t
   const int64_t b0 = (int64_t)blockIdx.x * (32 * NW) + 32 * wv;
   if (t < DT) se[t] = (i0 + t < n) ? ex[i0 + t] : 0;
   __syncthreads();
-  bool nonfinite = false;
+  bool wide = false;
 #pragma unroll
-  for (int q = 0; q < DT; ++q) nonfinite |= se[q] == DNONFINITE;
+  for (int q = 0; q < DT; ++q) wide |= se[q] == DWIDE;
+  // spins of samples b0 + 16 sb + r (clamped: results past B are never stored); the row padding meets
+  // zero digits
+  const int8_t* srow[2];
+#pragma unroll
+  for (int sb = 0; sb < 2; ++sb) srow[sb] = S + min(b0 + 16 * sb + r, B - 1) * lds;
+  if (__builtin_amdgcn_readfirstlane(wide)) {
+    doublex4_t y[IB][2];
+    dense_rows_f64<IB>(n, J, i0, srow, y);
+    dense_store_f64<IB>(n, i0, srow, y, b0, B, part + (int64_t)blockIdx.y * B);
+    return;
+  }
   // quad u of the thread: row tr + (4 NW) u, columns 4 tq .. 4 tq + 3 of the step.  Addresses are
   // clamped into the matrix and entries masked when they are converted, so that a load has a step
   // or two to arrive.
@@ -398,11 +501,6 @@ __global__ __launch_bounds__(64 * NW, 2) void energy_dense_kernel(int n, int64_t
       }
     }
   };
-  // spins of samples b0 + 16 sb + r (clamped: results past B are never stored); the row padding meets
-  // zero digits
-  const int8_t* srow[2];
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb) srow[sb] = S + min(b0 + 16 * sb + r, B - 1) * lds;
   i32x4_t sr[2][2];
   auto fetch_s = [&](int j0, i32x4_t(&v)[2]) {
 #pragma unroll
@@ -422,7 +520,7 @@ __global__ __launch_bounds__(64 * NW, 2) void energy_dense_kernel(int n, int64_t
 #pragma unroll
     for (int u = 0; u < NQ; ++u) {
       const int row = tr + 4 * NW * u, i = i0 + row, j = j0 + 4 * tq;
-      const int e = se[row] == DNONFINITE ? 0 : se[row];
+      const int e = se[row];
       uint2 d[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -488,12 +586,7 @@ __global__ __launch_bounds__(64 * NW, 2) void energy_dense_kernel(int n, int64_t
         double y = (double)acc[DD - 1][ib][sb][e];
 #pragma unroll
         for (int p = DD - 2; p >= 0; --p) y = fma(y, 256.0, (double)acc[p][ib][sb][e]);
-        if (!nonfinite || se[il] != DNONFINITE) {
-          y = ldexp(y, se[il] - 54);
-        } else {  // plain sums decide between NaN and the infinities
-          y = 0.0;
-          for (int j = i + 1; j < n; ++j) y += (double)J[(int64_t)i * n + j] * (double)srow[sb][j];
-        }
+        y = ldexp(y, se[il] - 54);
         if (i < n) v += (double)(int8_t)(sw >> (8 * e)) * y;
       }
     }
@@ -538,12 +631,12 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
   if (H.kind == VQMC_H_DENSE_F32) {
     int ntiles = (n + 15) / 16;
     int32_t* ex = (int32_t*)((double*)ws + (int64_t)ntiles * B);
+    hipError_t e;
+    auto groups = [&](int nw) { return (B + 32 * nw - 1) / (32 * nw); };
     energy_rowmax_kernel<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(n, H.J, ex);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     const bool vec = (n & 3) == 0 && ((uintptr_t)H.J & 15) == 0;
     // samples fastest: the longest row tiles start first
-    auto groups = [&](int nw) { return (B + 32 * nw - 1) / (32 * nw); };
     auto go = [&](auto kern, int nw) {
       kern<<<dim3((unsigned)groups(nw), (unsigned)ntiles), 64 * nw, 0, st>>>(n, lds, H.J, ex, S, B, (double*)ws);
       e = hipGetLastError();
