@@ -453,6 +453,21 @@ __device__ inline void dense_store_f64(int n, int i0, const int8_t* const (&srow
   }
 }
 
+// Every row in FP64: for couplings so few that the pass for the exponents costs more than the products
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void energy_dense_f64_kernel(int n, int64_t lds, const float* __restrict__ J,
+                                                                   const int8_t* __restrict__ S, int64_t B,
+                                                                   double* __restrict__ part) {
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i0 = blockIdx.y * 16;
+  const int64_t b0 = (int64_t)blockIdx.x * (32 * NW) + 32 * wv;
+  const int8_t* srow[2];
+#pragma unroll
+  for (int sb = 0; sb < 2; ++sb) srow[sb] = S + min(b0 + 16 * sb + (lane & 15), B - 1) * lds;
+  doublex4_t y[1][2];
+  dense_rows_f64<1>(n, J, i0, srow, y);
+  dense_store_f64<1>(n, i0, srow, y, b0, B, part + (int64_t)blockIdx.y * B);
+}
+
 // VEC: rows of J start 16-byte aligned (n a multiple of four and J 16-byte aligned)
 template <int NW, int IB, bool VEC>
 __global__ __launch_bounds__(64 * NW, 2) void energy_dense_kernel(int n, int64_t lds, const float* __restrict__ J,
@@ -615,6 +630,12 @@ __global__ void sum_partials_kernel(const double* __restrict__ part, int ntiles,
   E[b] = (s[0] + s[1]) + (s[2] + s[3]);
 }
 
+// Every row by energy_dense_f64_kernel up to so many sites and samples times 16-row tiles: a launch less (13.6 against
+// 16.6 us at n = 100, B = 1024); from about 200 sites the integer cores gain more (16.2 against 20.4 us at n = 255, B = 64),
+// and with more samples (27 against 18 us at n = 64, B = 65536)
+constexpr int kDenseF64Sites = 160;
+constexpr int64_t kDenseF64Work = 131072;
+
 // partial sums of the row tiles (of 16 rows at least), the rows' exponents
 size_t energy_dense_ws_bytes(int n, int64_t B) {
   return (size_t)((n + 15) / 16) * (size_t)B * sizeof(double) + (size_t)round_up((int64_t)n * 4, 256);
@@ -633,6 +654,12 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
     int32_t* ex = (int32_t*)((double*)ws + (int64_t)ntiles * B);
     hipError_t e;
     auto groups = [&](int nw) { return (B + 32 * nw - 1) / (32 * nw); };
+    if (n <= kDenseF64Sites && (int64_t)ntiles * B <= kDenseF64Work) {
+      energy_dense_f64_kernel<4><<<dim3((unsigned)groups(4), (unsigned)ntiles), 256, 0, st>>>(n, lds, H.J, S, B, (double*)ws);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+      sum_partials_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>((const double*)ws, ntiles, B, (double*)E);
+      return hipGetLastError();
+    }
     energy_rowmax_kernel<<<(unsigned)((n + 3) / 4), 256, 0, st>>>(n, H.J, ex);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const bool vec = (n & 3) == 0 && ((uintptr_t)H.J & 15) == 0;
