@@ -22,15 +22,18 @@ namespace vqmc {
 // accumulated exactly in int64 (integer weights) or in double (float weights, whose sums
 // of exact terms only differ from the oracle's by summation order).  A fixed thread -> row
 // map and fixed-shape reductions make the result deterministic.
+// SHARED: several lanes a row; without it the row loop is that of one lane.  64 registers, so that two workgroups share
+// a CU (float weights, degree 20, n = 3000, B = 16384: 152 against 219 us with 66; mean row 3, n = 1000: 43 against 66).
 constexpr int EMSE = 8;
 constexpr int EB_THREADS = 1024;
-template <typename WT, typename AT, bool RP_LDS>
-__global__ __launch_bounds__(EB_THREADS) void energy_csr_bits_kernel(int n, int64_t lds,
+template <typename WT, typename AT, bool RP_LDS, bool SHARED>
+__global__ __launch_bounds__(EB_THREADS, 8) void energy_csr_bits_kernel(int n, int64_t lds,
                                                                     const int64_t* __restrict__ rowptr,
                                                                     const int32_t* __restrict__ col,
                                                                     const WT* __restrict__ w,
                                                                     const int8_t* __restrict__ S, int64_t B,
-                                                                    int nst, int lanes, AT* __restrict__ E) {
+                                                                    int nst, int row_lanes, AT* __restrict__ E) {
+  const int lanes = SHARED ? row_lanes : 1;
   // nst bytes of site bits, then the row pointer (n + 1 int32, if staged), then scratch
   extern __shared__ __attribute__((aligned(16))) uint8_t shb[];
   uint8_t* bits = shb;
@@ -718,11 +721,13 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
                                          (int64_t*)E);
       return hipGetLastError();
     }
-    if (rp_lds) go(energy_csr_bits_kernel<int32_t, int64_t, true>, (const int32_t*)H.w, (int64_t*)E);
-    else go(energy_csr_bits_kernel<int32_t, int64_t, false>, (const int32_t*)H.w, (int64_t*)E);
+    auto kern = lanes > 1 ? (rp_lds ? energy_csr_bits_kernel<int32_t, int64_t, true, true> : energy_csr_bits_kernel<int32_t, int64_t, false, true>)
+                          : (rp_lds ? energy_csr_bits_kernel<int32_t, int64_t, true, false> : energy_csr_bits_kernel<int32_t, int64_t, false, false>);
+    go(kern, (const int32_t*)H.w, (int64_t*)E);
   } else {
-    if (rp_lds) go(energy_csr_bits_kernel<float, double, true>, (const float*)H.w, (double*)E);
-    else go(energy_csr_bits_kernel<float, double, false>, (const float*)H.w, (double*)E);
+    auto kern = lanes > 1 ? (rp_lds ? energy_csr_bits_kernel<float, double, true, true> : energy_csr_bits_kernel<float, double, false, true>)
+                          : (rp_lds ? energy_csr_bits_kernel<float, double, true, false> : energy_csr_bits_kernel<float, double, false, false>);
+    go(kern, (const float*)H.w, (double*)E);
   }
   return e;
 }
