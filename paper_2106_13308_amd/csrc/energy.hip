@@ -152,14 +152,13 @@ __global__ __launch_bounds__(EB_THREADS, 8) void energy_csr_bits_kernel(int n, i
 //
 // What bounds it: the address coalescing of the rows' loads (16 cycles a load instruction when the lanes lie
 // apart), then their latency.  So a lane takes four edges by one 16-byte load of each array, and
-// four rows at a time with their loads issued together.  Measured (us; before: a thread per row, two
+// EC_RB = 4 (or 2) rows at a time with their loads issued together.  Measured (us; before: a thread per row, two
 // edges a step, 64-bit sums per row): n = 500, 75 % of the edges, B = 1024: 35 -> 18; n = 10000, degree 10, B = 2048:
 // 41 -> 30.
-constexpr int EC_RB = 4;
 constexpr int EC_U = 4;
 typedef __attribute__((ext_vector_type(2))) short s16x2_t;
-template <bool RP_LDS>
-__global__ __launch_bounds__(EB_THREADS) void energy_csr_bytes_kernel(int n, int64_t lds,
+template <bool RP_LDS, int EC_RB>
+__global__ __launch_bounds__(EB_THREADS, EC_RB == 2 ? 8 : 4) void energy_csr_bytes_kernel(int n, int64_t lds,
                                                                      const int64_t* __restrict__ rowptr,
                                                                      const int32_t* __restrict__ col,
                                                                      const int32_t* __restrict__ w, int64_t nnz,
@@ -756,7 +755,11 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
     if (H.nnz >= EC_U && H.nnz < (int64_t)1 << 30 && swb + redb <= 160 * 1024) {
       const bool rpl = swb + rpb + redb <= 160 * 1024;
       const size_t sb = swb + (rpl ? rpb : 0) + redb;
-      auto kern = rpl ? energy_csr_bytes_kernel<true> : energy_csr_bytes_kernel<false>;
+      // two workgroups a CU where there is work and LDS for them, two rows at a time then (64 registers): n = 500, 8 % of the
+      // edges, B = 16384: 42 against 74 us; one workgroup a CU: four rows, 17 against 29 us at n = 16000, degree 6, B = 1
+      const bool pair = grid > 256 && 2 * sb <= 160 * 1024;
+      auto kern = pair ? (rpl ? energy_csr_bytes_kernel<true, 2> : energy_csr_bytes_kernel<false, 2>)
+                       : (rpl ? energy_csr_bytes_kernel<true, 4> : energy_csr_bytes_kernel<false, 4>);
       if ((e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sb)) !=
           hipSuccess)
         return e;
