@@ -368,12 +368,12 @@ __global__ __launch_bounds__(E::NT, OCC) void b_out_kernel(const bf16_t* __restr
   __shared__ float rowacc[E::WGN][E::BM];
   __shared__ float colacc[E::WGM][E::BN];
   const int t = threadIdx.x, lane = t & 63;
-  // the site tiles go round the XCDs: the weights are the larger operand
-  const int nsite = (n + E::BN - 1) / E::BN, nbat = (int)((B + E::BM - 1) / E::BM);
-  const int w = blockIdx.x, wq = __builtin_amdgcn_readfirstlane((w >> 3) / nbat);
-  const int tile = nsite - 1 - ((w & 7) + 8 * wq);  // later sites see more units: they come first
-  const int mt = (w >> 3) - nbat * wq;
-  if (tile < 0) return;
+  // eight site tiles at a time go round the XCDs (the weights are the larger operand), those left over run through
+  // their batch tiles in order; later sites see more units and come first
+  const int nsite = (n + E::BN - 1) / E::BN, nbat = (int)((B + E::BM - 1) / E::BM), dealt = (nsite & ~7) * nbat;
+  const int w = blockIdx.x, v = w < dealt ? w >> 3 : w - dealt;
+  const int q = __builtin_amdgcn_readfirstlane(v / nbat), mt = v - nbat * q;
+  const int tile = nsite - 1 - (w < dealt ? (w & 7) + 8 * q : (nsite & ~7) + q);
   const int64_t m0 = (int64_t)mt * E::BM;
   const int d0 = tile * E::BN;
   const typename E::Op oa{R, ldh, m0, B}, ob{P, ldh, d0, n};
@@ -705,7 +705,7 @@ hipError_t launch_b_logp(const vqmc_made& m, const int8_t* S, int64_t B, const b
   using E = BOut;
   const int64_t ldn = round_up(m.n, kPad), ldh = round_up(m.h, kPad), ldB = round_up(B, kPad);
   *nparts = (m.n + E::BN - 1) / E::BN;
-  b_out_kernel<E, false><<<b_grid(*nparts, (B + E::BM - 1) / E::BM), E::NT, 0, st>>>(
+  b_out_kernel<E, false><<<(unsigned)(*nparts * b_tiles(B, E::BM)), E::NT, 0, st>>>(
       R, ldh, (const bf16_t*)m.P, m.b2, m.c, m.n, m.h, B, S, ldn, lp_part, Z, nullptr, nullptr, nullptr, nullptr, ldB,
       nullptr);
   return hipGetLastError();
@@ -716,7 +716,7 @@ hipError_t launch_b_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, con
   using E = BOut;
   const int64_t ldn = round_up(m.n, kPad), ldh = round_up(m.h, kPad), ldB = round_up(B, kPad);
   *np2 = (int)((B + E::BM - 1) / E::BM);
-  b_out_kernel<E, true><<<b_grid((m.n + E::BN - 1) / E::BN, *np2), E::NT, 0, st>>>(
+  b_out_kernel<E, true><<<(unsigned)(b_tiles(m.n, E::BN) * *np2), E::NT, 0, st>>>(
       R, ldh, (const bf16_t*)m.P, m.b2, m.c, m.n, m.h, B, S, ldn, nullptr, nullptr, coef, G, Gt, St, ldB, db2_part);
   return hipGetLastError();
 }
