@@ -721,6 +721,44 @@ size_t logprob_ws_bytes(int n, int h, int64_t B, int dtype, bool backward) {
 }
 size_t sample_plain_ws_bytes(int n, int h, int64_t B, int dtype) { return layout(n, h, B, dtype, 2).total; }
 
+// The staged engine's layers.  R = relu(A) by sample and, if Rt, by unit (h x ldB).
+template <typename T>
+static hipError_t staged_hidden(const vqmc_made& m, const Geom& g, const int8_t* S, T* R, T* Rt, hipStream_t st) {
+  const dim3 grid(g.nt_h, g.mt_h);
+  if (Rt)
+    fwd_hidden_kernel<T, true><<<grid, 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n, m.h, g.B, R, g.ldh,
+                                                      Rt, g.ldB);
+  else
+    fwd_hidden_kernel<T, false><<<grid, 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n, m.h, g.B, R, g.ldh,
+                                                       nullptr, g.ldB);
+  return hipGetLastError();
+}
+// log sigma partials (g.nt_o rows of B) and, if Z, the logits
+template <typename T>
+static hipError_t staged_logp(const vqmc_made& m, const Geom& g, const int8_t* S, const T* R, float* lp_part, float* Z,
+                              hipStream_t st) {
+  fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
+      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, g.B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr, nullptr,
+      nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
+  return hipGetLastError();
+}
+
+// Which layers of log pi the staged engine takes: its tiles start faster, so it is ahead where they are many
+// and short, a few K steps each (us, staged against gemm_f32.hip / gemm_bf16.hip).
+// BF16, a layer at a time: n = 20, h = 200, B = 131072 first layer 54 / 78; n = 128, h = 1000, B = 16384 first
+// layer 63 / 72 (n = 200: 1.2 the other way); n = 20, h = 45, B = 131072 second layer 17 / 24 (h = 100: even).
+static bool staged_hidden_bf16(const Geom& g) {
+  return g.n <= 64 || (g.n <= 128 && (int64_t)g.mt_h * g.nt_h >= 1024);
+}
+static bool staged_logp_bf16(const Geom& g) { return g.n <= 64 && g.h <= 64; }
+// FP32, both layers (they pass relu(A) on in layouts of their own): n = 20, h = 200, B = 131072: 113 / 163;
+// n = 300, h = 45, B = 131072: 202 / 236; n = 2, h = 45, B = 16384: 14 / 19, n = 20, h = 500: 47 / 50, the other way
+// where the FP32 products have just turned to their large tiles (64 < h <= 128) and for fewer samples.
+static bool staged_f32(const Geom& g) {
+  if (g.n <= 64 && g.B >= 16384 && (g.B >= 32768 || g.h <= 64 || g.h > 128)) return true;
+  return g.B >= 65536 && (g.n <= 320 ? g.n <= 128 || g.h <= 256 : g.h <= 64);
+}
+
 template <typename T>
 static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, float* logp, float* Z,
                             void* ws, hipStream_t st) {
@@ -730,19 +768,23 @@ static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   T* R = (T*)(w + L.R);
   float* lp_part = (float*)(w + L.lp_part);
   hipError_t e;
+  int np = g.nt_o;
   if constexpr (sizeof(T) == 4) {
-    int np = 0;
-    if ((e = launch_f32_hidden(m, S, B, nullptr, R, B, false, st)) != hipSuccess) return e;  // by unit, h x B
-    if ((e = launch_f32_logp(m, S, B, R, B, lp_part, Z, &np, st)) != hipSuccess) return e;
-    sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
-    return hipGetLastError();
+    if (staged_f32(g)) {
+      if ((e = staged_hidden<T>(m, g, S, R, nullptr, st)) != hipSuccess) return e;
+      if ((e = staged_logp<T>(m, g, S, R, lp_part, Z, st)) != hipSuccess) return e;
+    } else {
+      if ((e = launch_f32_hidden(m, S, B, nullptr, R, B, false, st)) != hipSuccess) return e;  // by unit, h x B
+      if ((e = launch_f32_logp(m, S, B, R, B, lp_part, Z, &np, st)) != hipSuccess) return e;
+    }
   } else {
-    int np = 0;
-    if ((e = launch_b_hidden(m, S, B, R, nullptr, nullptr, st)) != hipSuccess) return e;
-    if ((e = launch_b_logp(m, S, B, R, lp_part, Z, &np, st)) != hipSuccess) return e;
-    sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
-    return hipGetLastError();
+    e = staged_hidden_bf16(g) ? staged_hidden<T>(m, g, S, R, nullptr, st) : launch_b_hidden(m, S, B, R, nullptr, nullptr, st);
+    if (e != hipSuccess) return e;
+    e = staged_logp_bf16(g) ? staged_logp<T>(m, g, S, R, lp_part, Z, st) : launch_b_logp(m, S, B, R, lp_part, Z, &np, st);
+    if (e != hipSuccess) return e;
   }
+  sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
+  return hipGetLastError();
 }
 
 template <typename T>
