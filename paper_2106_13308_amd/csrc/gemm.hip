@@ -743,6 +743,30 @@ static hipError_t staged_logp(const vqmc_made& m, const Geom& g, const int8_t* S
   return hipGetLastError();
 }
 
+// G, Gt, St and db2 partials (g.mt_o rows of ld(n)) for coef
+template <typename T>
+static hipError_t staged_out_grad(const vqmc_made& m, const Geom& g, const int8_t* S, const T* R, const float* coef,
+                                  float* lp_part, T* G, T* Gt, T* St, float* db2_part, hipStream_t st) {
+  fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
+      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, g.B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, coef, G, Gt, St, g.ldB,
+      db2_part, 0, 0, 0, 0, 0, nullptr);
+  return hipGetLastError();
+}
+// Dt and db1 partials (g.mt_h rows of ld(h))
+template <typename T>
+static hipError_t staged_adjoint(const vqmc_made& m, const Geom& g, const T* G, const T* Rt, T* Dt, float* db1_part,
+                                 hipStream_t st) {
+  bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, g.B, Rt, Dt, g.ldB,
+                                                             db1_part, g.ldh);
+  return hipGetLastError();
+}
+
+// The direct-to-LDS loads of gemm_bf16.hip take 16 bytes a lane from 16-byte aligned rows.  The calls ask for no
+// alignment of the spins and weights, so whatever lies otherwise goes through the staged kernels, whose loads may.
+static bool rows_aligned(const vqmc_made& m, const void* ws, const int8_t* S = nullptr) {
+  return (((uintptr_t)m.P | (uintptr_t)m.Pt | (uintptr_t)ws | (uintptr_t)S) & 15) == 0;
+}
+
 // Which layers of log pi the staged engine takes: its tiles start faster, so it is ahead where they are many
 // and short, a few K steps each (us, staged against gemm_f32.hip / gemm_bf16.hip).
 // BF16, a layer at a time: n = 20, h = 200, B = 131072 first layer 54 / 78; n = 128, h = 1000, B = 16384 first
@@ -778,9 +802,10 @@ static hipError_t logprob_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
       if ((e = launch_f32_logp(m, S, B, R, B, lp_part, Z, &np, st)) != hipSuccess) return e;
     }
   } else {
-    e = staged_hidden_bf16(g) ? staged_hidden<T>(m, g, S, R, nullptr, st) : launch_b_hidden(m, S, B, R, nullptr, nullptr, st);
+    const bool aligned = rows_aligned(m, ws, S);
+    e = !aligned || staged_hidden_bf16(g) ? staged_hidden<T>(m, g, S, R, nullptr, st) : launch_b_hidden(m, S, B, R, nullptr, nullptr, st);
     if (e != hipSuccess) return e;
-    e = staged_logp_bf16(g) ? staged_logp<T>(m, g, S, R, lp_part, Z, st) : launch_b_logp(m, S, B, R, lp_part, Z, &np, st);
+    e = !aligned || staged_logp_bf16(g) ? staged_logp<T>(m, g, S, R, lp_part, Z, st) : launch_b_logp(m, S, B, R, lp_part, Z, &np, st);
     if (e != hipSuccess) return e;
   }
   sum_rows_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(lp_part, np, B, B, logp);
@@ -812,12 +837,17 @@ static hipError_t backward_t(const vqmc_made& m, const int8_t* S, int64_t B, con
     if ((e = launch_f32_adjoint(m, B, Gt, Rt, Dt, nullptr, nullptr, db1_part, &np1, st)) != hipSuccess) return e;
     return launch_f32_weight(m, S, B, G, R, Dt, dP, db2_part, np2, db1_part, np1, db2, db1, st);
   } else {
-    int np1 = 0, np2 = 0;
-    if ((e = launch_b_hidden(m, S, B, R, Rt, nullptr, st)) != hipSuccess) return e;
+    const bool aligned = rows_aligned(m, ws, S);
+    int np1 = g.mt_h, np2 = g.mt_o;
+    e = aligned ? launch_b_hidden(m, S, B, R, Rt, nullptr, st) : staged_hidden<T>(m, g, S, R, Rt, st);
+    if (e != hipSuccess) return e;
     // the first product does not read coef; it may overlap the work that produces it
     if (coef_ready && (e = hipStreamWaitEvent(st, coef_ready, 0)) != hipSuccess) return e;
-    if ((e = launch_b_out_grad(m, S, B, R, coef, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
-    if ((e = launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st)) != hipSuccess) return e;
+    e = aligned ? launch_b_out_grad(m, S, B, R, coef, G, Gt, St, db2_part, &np2, st)
+                : staged_out_grad<T>(m, g, S, R, coef, lp_part, G, Gt, St, db2_part, st);
+    if (e != hipSuccess) return e;
+    e = aligned ? launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st) : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
+    if (e != hipSuccess) return e;
     return launch_b_weight(m, B, Gt, St, Rt, Dt, dP, db2_part, np2, db1_part, np1, db2, db1, st);
   }
 }
@@ -835,11 +865,11 @@ size_t sr_gram_ws_bytes(int n, int h, int64_t B, int dtype) {
 
 // The hidden adjoint of the Gram's factors
 template <typename T>
-static hipError_t sr_hidden_adjoint(const vqmc_made& m, int64_t B, const T* G, const T* Gt, const T* Rt, T* Dt,
-                                    float* db1_part, hipStream_t st) {
+static hipError_t sr_hidden_adjoint(const vqmc_made& m, const Geom& g, bool aligned, const T* G, const T* Gt, const T* Rt,
+                                    T* Dt, float* db1_part, hipStream_t st) {
   int np1 = 0;
-  if constexpr (sizeof(T) == 4) return launch_f32_adjoint(m, B, Gt, Rt, nullptr, Dt, nullptr, db1_part, &np1, st);
-  else return launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st);
+  if constexpr (sizeof(T) == 4) return launch_f32_adjoint(m, g.B, Gt, Rt, nullptr, Dt, nullptr, db1_part, &np1, st);
+  else return aligned ? launch_b_adjoint(m, g.B, G, Rt, Dt, db1_part, &np1, st) : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
 }
 
 template <typename T>
@@ -859,6 +889,7 @@ static hipError_t sr_gram_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
   const size_t xo = sr_extra_offset(m.n, m.h, B, m.wdtype);
   float* ones = (float*)(w + xo);
   float* parts = (float*)(w + xo + round_up(B * 4, 256));
+  const bool aligned = rows_aligned(m, ws, S);
   hipError_t e;
   fill_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(ones, B, 1.f);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -868,10 +899,13 @@ static hipError_t sr_gram_t(const vqmc_made& m, const int8_t* S, int64_t B, floa
     if ((e = launch_f32_out_grad(m, S, B, Rt, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
   } else {
     int np2 = 0;
-    if ((e = launch_b_hidden(m, S, B, R, Rt, nullptr, st)) != hipSuccess) return e;
-    if ((e = launch_b_out_grad(m, S, B, R, ones, G, Gt, St, db2_part, &np2, st)) != hipSuccess) return e;
+    e = aligned ? launch_b_hidden(m, S, B, R, Rt, nullptr, st) : staged_hidden<T>(m, g, S, R, Rt, st);
+    if (e != hipSuccess) return e;
+    e = aligned ? launch_b_out_grad(m, S, B, R, ones, G, Gt, St, db2_part, &np2, st)
+                : staged_out_grad<T>(m, g, S, R, ones, lp_part, G, Gt, St, db2_part, st);
+    if (e != hipSuccess) return e;
   }
-  if ((e = sr_hidden_adjoint<T>(m, B, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
+  if ((e = sr_hidden_adjoint<T>(m, g, aligned, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   return launch_sr_gram_sweeps(m.wdtype, Gt, Rt, Dt, St, g.ldB, m.c, m.n, m.h, B, parts, K, st, G, S, g.ldn);
 }
 
@@ -898,7 +932,7 @@ static hipError_t sr_gram_sampled_t(const vqmc_made& m, const int8_t* S, int64_t
   if ((e = hipGetLastError()) != hipSuccess) return e;
   grad_out_kernel<T><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(Zs, S, g.ldn, ones, m.n, B, G, Gt, St, g.ldB, db2_part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = sr_hidden_adjoint<T>(m, B, G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
+  if ((e = sr_hidden_adjoint<T>(m, g, rows_aligned(m, ws), G, Gt, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   return launch_sr_gram_sweeps(m.wdtype, Gt, Rt, Dt, St, g.ldB, m.c, m.n, m.h, B, parts, K, st, G, S, g.ldn);
 }
 
@@ -968,16 +1002,9 @@ static hipError_t sr_jvp_t(const vqmc_made& m, const int8_t* S, int64_t B, const
   fill_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>(ones, B, 1.f);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // score factors: R (and Rt), G with coef = 1, D
-  fwd_hidden_kernel<T, true><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c,
-                                                                    m.n, m.h, B, R, g.ldh, Rt, g.ldB);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  fwd_out_kernel<T, 1><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-      R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, nullptr, ones, G, Gt,
-      St, g.ldB, db2_part, 0, 0, 0, 0, 0, nullptr);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  bwd_hidden_kernel<T><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(G, g.ldn, (const T*)m.Pt, m.c, m.n, m.h, B, Rt, Dt,
-                                                             g.ldB, db1_part, g.ldh);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = staged_hidden<T>(m, g, S, R, Rt, st)) != hipSuccess) return e;
+  if ((e = staged_out_grad<T>(m, g, S, R, ones, lp_part, G, Gt, St, db2_part, st)) != hipSuccess) return e;
+  if ((e = staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st)) != hipSuccess) return e;
   // the direction in the kernels' layouts
   if ((e = launch_cast(m.n, m.h, gP, m.wdtype, gPw, gPtw, st)) != hipSuccess) return e;
   // U = gb2 + R (masked gW2)^T
@@ -1020,8 +1047,10 @@ static hipError_t backward_sampled_t(const vqmc_made& m, const int8_t* S, int64_
                                                            sizeof(T) == 2 ? St : nullptr, g.ldB, db2_part);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if constexpr (sizeof(T) == 2) {
-    int np1 = 0;
-    if ((e = launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st)) != hipSuccess) return e;
+    int np1 = g.mt_h;
+    e = rows_aligned(m, ws) ? launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st)
+                            : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
+    if (e != hipSuccess) return e;
     return launch_b_weight(m, B, Gt, St, Rt, Dt, dP, db2_part, g.mt_o, db1_part, np1, db2, db1, st);
   } else {
     int np1 = 0;
@@ -1083,23 +1112,19 @@ static hipError_t tim_forward_t(const vqmc_made& m, const int8_t* S, int64_t B, 
   uint8_t* w = (uint8_t*)ws;
   T* R = (T*)(w + L.R);
   float* lp_part = (float*)(w + L.lp_part);
+  hipError_t e;
   if constexpr (sizeof(T) == 2) {
-    hipError_t e = launch_b_hidden(m, S, B, R, nullptr, A, st);
-    int np = 0;
-    return e != hipSuccess ? e : launch_b_logp(m, S, B, R, lp_part, Z, &np, st);
-  } else {
-    fwd_hidden_kernel<T, false><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n,
-                                                                       m.h, B, R, g.ldh, nullptr, g.ldB);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    fwd_out_kernel<T, 0><<<dim3(g.nt_o, g.mt_o), 256, 0, st>>>(
-        R, g.ldh, (const T*)m.P, m.b2, m.c, m.n, m.h, B, (int8_t*)S, g.ldn, g.ldn, lp_part, Z, nullptr, nullptr,
-        nullptr, nullptr, g.ldB, nullptr, 0, 0, 0, 0, 0, nullptr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    fwd_hidden_kernel<T, false, false, float><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(
-        S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n, m.h, B, A, g.ldh, (T*)nullptr, g.ldB);
-    return hipGetLastError();
+    if (rows_aligned(m, ws, S)) {
+      int np = 0;
+      e = launch_b_hidden(m, S, B, R, nullptr, A, st);
+      return e != hipSuccess ? e : launch_b_logp(m, S, B, R, lp_part, Z, &np, st);
+    }
   }
+  if ((e = staged_hidden<T>(m, g, S, R, nullptr, st)) != hipSuccess) return e;
+  if ((e = staged_logp<T>(m, g, S, R, lp_part, Z, st)) != hipSuccess) return e;
+  fwd_hidden_kernel<T, false, false, float><<<dim3(g.nt_h, g.mt_h), 256, 0, st>>>(
+      S, g.ldn, (const T*)m.Pt, g.ldn, m.b1, m.c, m.n, m.h, B, A, g.ldh, (T*)nullptr, g.ldB);
+  return hipGetLastError();
 }
 
 hipError_t launch_tim_forward(const vqmc_made& m, const int8_t* S, int64_t B, float* Z, float* A, void* ws,
