@@ -54,6 +54,10 @@ __device__ inline double* chol_diag(double* A, int64_t ld, int nb, int i) {
   return A + (int64_t)i * CB * ld + (int64_t)min(i + 1, nb - 1) * CB;
 }
 
+// The counter that deals the blocks of the back substitution: in the first diagonal block, which is free once its
+// factor lies beside it (nb > 1); cleared by the second step
+__device__ inline int* chol_ticket(double* A) { return (int*)A; }
+
 // 1 / sqrt(d): the hardware estimate (about 24 bits) and one step of third order,
 // r (1 + e/2 + 3 e^2/8) with e = 1 - d r^2, accurate to a few ulp; NaN for d <= 0.
 __device__ inline double chol_rsqrt(double d) {
@@ -325,6 +329,7 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
     }
     __syncthreads();
   }
+  if (j == 0 && t == 64 * CW - 1 && (int)blockIdx.x == npanel - 1) *chol_ticket(A) = 0;
   if (w < 4 && (int)blockIdx.x == npanel - 1) {
     // the diagonal block's factor goes to its own place: other workgroups may still be reading the block
     double* L = chol_diag(A, ld, nb, j + 1);
@@ -335,12 +340,14 @@ __global__ __launch_bounds__(64 * CW) void chol_step_kernel(double* __restrict__
   }
 }
 
-// Back substitution: workgroup x solves block i = nb - 1 - x of L^T y = w,
+// Back substitution: the x-th workgroup to start solves block i = nb - 1 - x of L^T y = w,
 //   y_i = L_ii^-T (w_i - sum_{j > i} L_ji^T y_j),
-// taking the later blocks' y_j as they appear in memory.  It only waits for workgroups before it in
-// the grid, which are dispatched first, so the waits end in whatever number the workgroups run at a
-// time; a wait is bounded all the same (kSpin polls, then NaN).  An entry of y is published by one
-// 8-byte store over the kUnknown that chol_init_kernel left, so no flag or fence is needed.  The chain
+// taking the later blocks' y_j as they appear in memory.  A workgroup draws its x when it runs, so it only waits for
+// workgroups that run already or have ended: the waits end whatever the order in which workgroups are dispatched, and
+// with other solves on other streams.  (By blockIdx, two solves could each hold one XCD's slots with workgroups that wait
+// for ones the other keeps out of another XCD.)  A wait is bounded all the same: after kSpin polls, seconds, the
+// workgroup goes on with NaN, and y is NaN from there on, as for a matrix that is not positive definite.  An entry of y
+// is published by one 8-byte store over the kUnknown that chol_init_kernel left, so no flag or fence is needed.  The chain
 // per block is one such hand-over and two 64 x 64 matrix-vector products: the inverse of L_ii is
 // formed before the first wait and the next L_ji is loaded before its y_j is awaited.
 constexpr int kSpin = 1 << 22;
@@ -350,8 +357,11 @@ __global__ __launch_bounds__(256) void chol_back_kernel(double* __restrict__ A, 
   __shared__ __align__(16) double X[CB][CL];  // L_ii^-1
   __shared__ double part[4][CB];
   __shared__ double v[CB];
+  __shared__ int ticket;
   const int t = threadIdx.x, c = t & 63, q = t >> 6;
-  const int i = nb - 1 - (int)blockIdx.x;
+  if (t == 0) ticket = nb > 1 ? __hip_atomic_fetch_add(chol_ticket(A), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+  __syncthreads();
+  const int i = nb - 1 - __builtin_amdgcn_readfirstlane(ticket);
   const int64_t i0 = (int64_t)i * CB;
   const double* Ld = chol_diag(A, ld, nb, i);
   for (int e = t; e < CB * CB; e += 256) L[e >> 6][e & 63] = Ld[(e >> 6) * ld + (e & 63)];
@@ -374,13 +384,16 @@ __global__ __launch_bounds__(256) void chol_back_kernel(double* __restrict__ A, 
     for (int e = 0; e < 16; ++e) l[e] = p[(int64_t)e * ld];
   };
   if (nb - 1 > i) fetch(nb - 1);
+  int spin = kSpin;
   for (int jj = nb - 1; jj > i; --jj) {
     unsigned long long* src = y + (int64_t)jj * CB + 16 * q + (c & 15);
     unsigned long long u = kUnknown;
-    for (int n = 0; n < kSpin; ++n) {
+    int n = 0;
+    for (; n < spin; ++n) {
       u = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (__ballot(u == kUnknown) == 0) break;
     }
+    if (n == spin) spin = 1;  // the result is lost: no second wait
     const double yv = __longlong_as_double((long long)u);
 #pragma unroll
     for (int e = 0; e < 16; ++e) sum = fma(l[e], chol_bcast(yv, e), sum);
