@@ -90,7 +90,8 @@ __device__ inline void chol_frag(const double* row, double (&v)[NK]) {
 
 // acc -= (src of lane N of the lane's row of 16) * mul.  The DPP read of src needs two wait states after
 // the instruction that wrote it, which the compiler does not see in here: chol_scale and
-// chol_next, the only writers of a src, end with them.
+// chol_next, the only writers of a src, end with them.  (tests/test_dpp_wait_states.py reads the built assembly for copies
+// that the register allocator might put in between.)
 template <int N>
 __device__ inline void chol_fnma_row(double& acc, double src, double mul) {
   __asm__("v_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf" : "+v"(acc) : "v"(src), "v"(mul), "n"(N));
