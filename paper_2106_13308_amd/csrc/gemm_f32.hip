@@ -114,7 +114,7 @@ struct FPairs {
 
 enum FMask { F_ALL, F_BELOW, F_FROM };  // ks of a row that count: all, those below its limit, those from it on
 
-// Operand X[k][row] (T = float, or int8_t spins), rows adjacent, kmax ks (those past the end read as zero: the
+// Operand X[k][row] (T = float, or int8_t spins), rows adjacent, row0 < ld, kmax ks (those past the end read as zero: the
 // buffer descriptor of a run ends with the matrix), the ks of a run in the order of ORDER
 template <typename T, class ORDER, FMask MASK = F_ALL>
 struct FCols {
@@ -259,7 +259,9 @@ __global__ __launch_bounds__(E::NT) void f32_out_kernel(const float* __restrict_
     cb[i] = (GRAD && ok) ? coef[b] : 0.f;
   }
   const int dl = d0 + E::col0() + (t & 31);
-  e.run(FCols<float, FPairs>(Rt, ldB, m0 + E::row0(), h),
+  // (the tile's second rows may start past an unpadded batch: their results are not stored, but the rows must lie in the
+  // matrix for its descriptor to end with it)
+  e.run(FCols<float, FPairs>(Rt, ldB, min(m0 + E::row0(), ldB - 1), h),
         FCols<float, FPairs, F_BELOW>(Pt, ldn, d0 + E::col0(), h, dl < n ? c[dl] : 0, c[d0]),  // unit k feeds site d iff k < c[d]
         0, c[min(d0 + E::BN, n) - 1]);
 #pragma unroll
