@@ -1135,8 +1135,18 @@ hipError_t launch_tim_forward(const vqmc_made& m, const int8_t* S, int64_t B, fl
 
 hipError_t launch_logprob(const vqmc_made& m, const int8_t* S, int64_t B, float* logp, float* Z,
                           void* ws, hipStream_t st) {
-  if (m.wdtype == VQMC_BF16) return logprob_t<bf16_t>(m, S, B, logp, Z, ws, st);
-  return logprob_t<float>(m, S, B, logp, Z, ws, st);
+  // samples are independent: slices that keep grids and offsets within 32 bits whatever the batch (the workspace of B
+  // samples holds that of a slice)
+  constexpr int64_t kSlice = (int64_t)1 << 22;
+  const int64_t ldn = round_up(m.n, kPad);
+  for (int64_t b = 0; b < B; b += kSlice) {
+    const int64_t len = std::min(kSlice, B - b);
+    float* Zb = Z ? Z + b * ldn : nullptr;
+    const hipError_t e = m.wdtype == VQMC_BF16 ? logprob_t<bf16_t>(m, S + b * ldn, len, logp + b, Zb, ws, st)
+                                               : logprob_t<float>(m, S + b * ldn, len, logp + b, Zb, ws, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 hipError_t launch_backward(const vqmc_made& m, const int8_t* S, int64_t B, const float* coef,

@@ -106,11 +106,16 @@ struct F32 {
   }
 };
 
-// The step order of a run whose operands both have their rows adjacent
-struct FPairs {
-  static constexpr int KC = 16;
+// The step order of a run whose operands both have their rows adjacent.  A lane's offsets within a run have 32 bits: from
+// 2^31 / (4 * 15) columns of a matrix on (35.8 million samples), runs of two ks.
+template <int KC_>
+struct FPairsOf {
+  static constexpr int KC = KC_;
   __device__ static int k(int s, int g) { return 2 * s + g; }
 };
+using FPairs = FPairsOf<16>;
+using FFar = FPairsOf<2>;
+static bool f32_far(int64_t ld) { return (FPairs::KC - 1) * ld * (int64_t)sizeof(float) > 0x7FFFFFFF; }
 
 enum FMask { F_ALL, F_BELOW, F_FROM };  // ks of a row that count: all, those below its limit, those from it on
 
@@ -232,7 +237,7 @@ __global__ __launch_bounds__(E::NT) void f32_hidden_kernel(const int8_t* __restr
 // GRAD = false: log sigma partials (one row of B per site tile) and optionally Z (B x ldn).
 // GRAD = true: G = coef s sigma(-s z) by sample (B x ldn) and by site (Gt, n x ldB, zero past B), the
 // spins by site (St, the same, nullable), and db2 partials (one row of ldn per sample tile).
-template <class E, bool GRAD>
+template <class E, bool GRAD, class ORDER = FPairs>
 __global__ __launch_bounds__(E::NT) void f32_out_kernel(const float* __restrict__ Rt, int64_t ldB,
                                                         const float* __restrict__ Pt, int64_t ldn,
                                                         const float* __restrict__ b2, const int32_t* __restrict__ c,
@@ -261,8 +266,8 @@ __global__ __launch_bounds__(E::NT) void f32_out_kernel(const float* __restrict_
   const int dl = d0 + E::col0() + (t & 31);
   // (the tile's second rows may start past an unpadded batch: their results are not stored, but the rows must lie in the
   // matrix for its descriptor to end with it)
-  e.run(FCols<float, FPairs>(Rt, ldB, min(m0 + E::row0(), ldB - 1), h),
-        FCols<float, FPairs, F_BELOW>(Pt, ldn, d0 + E::col0(), h, dl < n ? c[dl] : 0, c[d0]),  // unit k feeds site d iff k < c[d]
+  e.run(FCols<float, ORDER>(Rt, ldB, min(m0 + E::row0(), ldB - 1), h),
+        FCols<float, ORDER, F_BELOW>(Pt, ldn, d0 + E::col0(), h, dl < n ? c[dl] : 0, c[d0]),  // unit k feeds site d iff k < c[d]
         0, c[min(d0 + E::BN, n) - 1]);
 #pragma unroll
   for (int i = 0; i < E::NI; ++i) {
@@ -303,7 +308,7 @@ __global__ __launch_bounds__(E::NT) void f32_out_kernel(const float* __restrict_
 // ---------------------------------------------------------------- hidden adjoint
 // [Rt > 0] (G P_lower) by sample (D, B x ldh) or by unit (Dt, h x ldB, zero past B), whichever is given, db1
 // partials (one row of ldh per sample tile) and, if R, relu(A) by sample from Rt.
-template <class E>
+template <class E, class ORDER = FPairs>
 __global__ __launch_bounds__(E::NT) void f32_adjoint_kernel(const float* __restrict__ Gt, int64_t ldB,
                                                             const float* __restrict__ P, int64_t ldh,
                                                             const int32_t* __restrict__ c, int n, int h, int64_t B,
@@ -324,8 +329,8 @@ __global__ __launch_bounds__(E::NT) void f32_adjoint_kernel(const float* __restr
     const int k = n0 + t / E::BM + i * (E::NT / E::BM);
     rv[i] = (k < h && m0 + m < ldB) ? Rt[(int64_t)k * ldB + m0 + m] : 0.f;
   }
-  e.run(FCols<float, FPairs>(Gt, ldB, m0 + E::row0(), n),
-        FCols<float, FPairs, F_FROM>(P, ldh, n0 + E::col0(), n, e.bound[E::col0() + (t & 31)], last), first, n);
+  e.run(FCols<float, ORDER>(Gt, ldB, m0 + E::row0(), n),
+        FCols<float, ORDER, F_FROM>(P, ldh, n0 + E::col0(), n, e.bound[E::col0() + (t & 31)], last), first, n);
 #pragma unroll
   for (int i = 0; i < E::NI; ++i) {
     const int nn = t / E::BM + i * (E::NT / E::BM), k = n0 + nn;
@@ -460,6 +465,7 @@ hipError_t launch_f32_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, c
                                                               nullptr, nullptr, coef, G, Gt, St, db2_part);
     return hipGetLastError();
   };
+  if (f32_far(ldB)) return go(f32_out_kernel<FLarge, true, FFar>, FLarge::BM, FLarge::BN, FLarge::NT);
   return f32_large(ldB, ldn) ? go(f32_out_kernel<FLarge, true>, FLarge::BM, FLarge::BN, FLarge::NT)
                              : go(f32_out_kernel<FSmall, true>, FSmall::BM, FSmall::BN, FSmall::NT);
 }
@@ -473,6 +479,7 @@ hipError_t launch_f32_adjoint(const vqmc_made& m, int64_t B, const float* Gt, co
                                                               R, db1_part);
     return hipGetLastError();
   };
+  if (f32_far(ldB)) return go(f32_adjoint_kernel<FLarge, FFar>, FLarge::BM, FLarge::BN, FLarge::NT);
   return f32_large(ldB, ldh) ? go(f32_adjoint_kernel<FLarge>, FLarge::BM, FLarge::BN, FLarge::NT)
                              : go(f32_adjoint_kernel<FSmall>, FSmall::BM, FSmall::BN, FSmall::NT);
 }
