@@ -190,8 +190,11 @@ struct SpRec {
 // cyc[(g * 12 + w) * 3] = cycles wave w of sample group g spent from leaving one block's barrier
 // to arriving at the next one's, summed over the blocks; [.. + 1] = cycles from the first
 // departure to the last; [.. + 2] = the same span in ticks of the 100 MHz constant clock.
+//
+// 128 registers, four waves a SIMD: a workgroup can start while the last waves of the one before it on the CU still
+// write (with 133 - 143: the draw with Zs and Rt at n = 2, h = 3, B = 16384 38.4 us, 33.8 so).
 template <typename WT, bool PLANES, bool TIMING>
-__global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
+__global__ __launch_bounds__(SP_THREADS, 4) void sample_pipe_kernel(
     const uint8_t* __restrict__ ztab, const uint8_t* __restrict__ utab, int nzt, int nut,
     const float* __restrict__ band, const float* __restrict__ b1, const float* __restrict__ b2,
     const int32_t* __restrict__ c,
@@ -338,11 +341,13 @@ __global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
         return fmaf(cp[3], p1.w, fmaf(cp[2], p1.z, fmaf(cp[1], p1.y, fmaf(cp[0], p1.x, 0.f))));
       };
       int ub = fprev - fprev % SP_PDS;
-      float4 a4 = *(const float4*)(arow + ub);
+      float4 a4;  // the group's states; with PLANES read and written without a register each in advance
+      if constexpr (!PLANES) a4 = *(const float4*)(arow + ub);
       auto group = [&](bool whole) {
+        if constexpr (PLANES) a4 = *(const float4*)(arow + ub);
         const float a0[4] = {a4.x, a4.y, a4.z, a4.w};
         const float ns = nsn;
-        a4 = *(const float4*)(arow + ub + SP_PDS);  // (past the block's units: not used)
+        if constexpr (!PLANES) a4 = *(const float4*)(arow + ub + SP_PDS);  // (past the block's units: not used)
         nsn = fetch_ns(whole || ub + SP_PDS <= fcur ? ub + SP_PDS : ub);
         float an[4], rl = 0.f, acc1 = 0.f;
         if (whole) acc1 = beside(ring[0].p1);
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
               zn[2] = fmaf(r.n2.z, rl, zn[2]); zn[3] = fmaf(r.n2.w, rl, zn[3]);
             }
             an[p] = a;
-            if (!whole) arow[u] = a;
+            if (PLANES || !whole) arow[u] = a;
             if constexpr (PLANES) {
               // exact three-term split of relu(a) by truncation (see sp_split3)
               const uint32_t x = __float_as_uint(rl);
@@ -430,7 +435,7 @@ __global__ __launch_bounds__(SP_THREADS) void sample_pipe_kernel(
           r.w2 = fetch(p, 1, next);
           if (!whole || p == SP_PDS - 1) r.n2 = fetch(p, 3, next);
         }
-        if (whole) *(float4*)(arow + ub) = make_float4(an[0], an[1], an[2], an[3]);
+        if (!PLANES && whole) *(float4*)(arow + ub) = make_float4(an[0], an[1], an[2], an[3]);
         ub += SP_PDS;
       };
       if (ub < fprev) group(false);
