@@ -248,7 +248,9 @@ __global__ __launch_bounds__(SP_THREADS, 4) void sample_pipe_kernel(
     const int s = tt >> 4, q4 = tt & 15;
     const int d = SP_T * blk + 4 * q4;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (d < n) {
+    // inside: every site of the block exists, so no selects (all blocks but the last; with few units a block these draws are
+    // its longest helper work: n = 10000, h = 100, BF16: 230 us, 240 with them)
+    auto draw = [&](bool inside) {
       const float4 u4 = site_uniforms(seed, step, tag, (uint64_t)(b0 + s + offset), (uint32_t)(d >> 2));
       const float uv[4] = {u4.x, u4.y, u4.z, u4.w};
 #pragma unroll
@@ -256,9 +258,11 @@ __global__ __launch_bounds__(SP_THREADS, 4) void sample_pipe_kernel(
         // s = +1 iff u < sigma(z) iff z > log(u) - log(1-u); u = 0 gives -inf (always +1).
         // 1 - u is exact for the 24-bit dyadic u.
         const float lg = __logf(uv[e]) - __logf(1.f - uv[e]);
-        v[e] = (d + e < n) ? -lg * SP_SCALE : 0.f;
+        v[e] = (inside || d + e < n) ? -lg * SP_SCALE : 0.f;
       }
-    }
+    };
+    if (SP_T * (blk + 1) <= n) draw(true);
+    else if (d < n) draw(false);
     *(float4*)(dst + s * SP_T + 4 * q4) = make_float4(v[0], v[1], v[2], v[3]);
   };
 
