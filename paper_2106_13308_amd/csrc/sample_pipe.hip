@@ -192,9 +192,10 @@ struct SpRec {
 // departure to the last; [.. + 2] = the same span in ticks of the 100 MHz constant clock.
 //
 // 128 registers, four waves a SIMD: a workgroup can start while the last waves of the one before it on the CU still
-// write (with 133 - 143: the draw with Zs and Rt at n = 2, h = 3, B = 16384 38.4 us, 33.8 so).
+// write (with 133 - 143: the draw with Zs and Rt at n = 2, h = 3, B = 16384 38.4 us, 33.8 so).  BF16 weights without planes,
+// that is many units and long sweeps, keep their 133 (n = h = 2000, B = 8192: 999 us, 1012 with 128).
 template <typename WT, bool PLANES, bool TIMING>
-__global__ __launch_bounds__(SP_THREADS, 4) void sample_pipe_kernel(
+__global__ __launch_bounds__(SP_THREADS, sizeof(WT) == 2 && !PLANES ? 3 : 4) void sample_pipe_kernel(
     const uint8_t* __restrict__ ztab, const uint8_t* __restrict__ utab, int nzt, int nut,
     const float* __restrict__ band, const float* __restrict__ b1, const float* __restrict__ b2,
     const int32_t* __restrict__ c,
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(SP_THREADS, 4) void sample_pipe_kernel(
     const int d = SP_T * blk + 4 * q4;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     // inside: every site of the block exists, so no selects (all blocks but the last; with few units a block these draws are
-    // its longest helper work: n = 10000, h = 100, BF16: 230 us, 240 with them)
+    // its longest helper work: n = 10000, h = 100, BF16: 230 us, 240 with them; without planes no gain)
     auto draw = [&](bool inside) {
       const float4 u4 = site_uniforms(seed, step, tag, (uint64_t)(b0 + s + offset), (uint32_t)(d >> 2));
       const float uv[4] = {u4.x, u4.y, u4.z, u4.w};
@@ -261,7 +262,7 @@ __global__ __launch_bounds__(SP_THREADS, 4) void sample_pipe_kernel(
         v[e] = (inside || d + e < n) ? -lg * SP_SCALE : 0.f;
       }
     };
-    if (SP_T * (blk + 1) <= n) draw(true);
+    if (PLANES && SP_T * (blk + 1) <= n) draw(true);
     else if (d < n) draw(false);
     *(float4*)(dst + s * SP_T + 4 * q4) = make_float4(v[0], v[1], v[2], v[3]);
   };
