@@ -846,7 +846,7 @@ static hipError_t backward_t(const vqmc_made& m, const int8_t* S, int64_t B, con
     e = aligned ? launch_b_out_grad(m, S, B, R, coef, G, Gt, St, db2_part, &np2, st)
                 : staged_out_grad<T>(m, g, S, R, coef, lp_part, G, Gt, St, db2_part, st);
     if (e != hipSuccess) return e;
-    e = aligned ? launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st) : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
+    e = aligned ? launch_b_adjoint(m, false, B, G, Rt, Dt, db1_part, &np1, st) : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
     if (e != hipSuccess) return e;
     return launch_b_weight(m, B, Gt, St, Rt, Dt, dP, db2_part, np2, db1_part, np1, db2, db1, st);
   }
@@ -869,7 +869,7 @@ static hipError_t sr_hidden_adjoint(const vqmc_made& m, const Geom& g, bool alig
                                     T* Dt, float* db1_part, hipStream_t st) {
   int np1 = 0;
   if constexpr (sizeof(T) == 4) return launch_f32_adjoint(m, g.B, Gt, Rt, nullptr, Dt, nullptr, db1_part, &np1, st);
-  else return aligned ? launch_b_adjoint(m, g.B, G, Rt, Dt, db1_part, &np1, st) : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
+  else return aligned ? launch_b_adjoint(m, true, g.B, G, Rt, Dt, db1_part, &np1, st) : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
 }
 
 template <typename T>
@@ -1048,7 +1048,7 @@ static hipError_t backward_sampled_t(const vqmc_made& m, const int8_t* S, int64_
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if constexpr (sizeof(T) == 2) {
     int np1 = g.mt_h;
-    e = rows_aligned(m, ws) ? launch_b_adjoint(m, B, G, Rt, Dt, db1_part, &np1, st)
+    e = rows_aligned(m, ws) ? launch_b_adjoint(m, true, B, G, Rt, Dt, db1_part, &np1, st)
                             : staged_adjoint<T>(m, g, G, Rt, Dt, db1_part, st);
     if (e != hipSuccess) return e;
     return launch_b_weight(m, B, Gt, St, Rt, Dt, dP, db2_part, g.mt_o, db1_part, np1, db2, db1, st);

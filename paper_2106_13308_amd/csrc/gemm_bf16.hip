@@ -18,7 +18,8 @@
 // Spins stay int8 up to the matrix operand: a row of a stage is 64 bytes, and the sign and lowest bit
 // of a byte are an FP8 number (+-2^-9 or 0) that one conversion with scale 2^9 makes a pair of BF16.
 // The staircase masks touch only the stages between the first and the last limit of the tile's rows:
-// there the weight operand is masked in registers, elsewhere it is used as loaded (no masked copies).
+// there the weight operand is masked in registers, elsewhere it is used as loaded (and everywhere where the adjoint
+// has the masked copy of the sampler's tables).
 //
 // What bounds it: the chain of stages of one tile.  The longest column of tiles launched alone takes 43 of the first
 // layer's 48 us and 50 of the adjoint's 54 (157 stages of 0.3 us: barrier, operand reads, products, the
@@ -36,6 +37,7 @@
 //   second layer, log p         53 (157)               17 (35)              78
 //   second layer, gradient                             21 (48)
 //   hidden adjoint              54 (70)                18 (66)              70 (75)
+//   ... with the masked copy    53                                          60
 //   weight and bias gradients   66 (78)                16 (72 + 9)          113 (123)
 #include "common.hpp"
 #include "kernels.hpp"
@@ -494,7 +496,8 @@ __global__ __launch_bounds__(E::NT, OCC) void b_out_kernel(const bf16_t* __restr
 }
 
 // ---------------------------------------------------------------- hidden adjoint
-// Dt = [Rt > 0] (G P_lower) by unit (h x ldB, zero past B) and db1 partials (one row of ldh per sample tile)
+// Dt = [Rt > 0] (G P_lower) by unit (h x ldB, zero past B) and db1 partials (one row of ldh per sample tile).  E::MASK =
+// B_ALL: Pt is the masked copy of P^T.
 template <class E>
 __global__ __launch_bounds__(E::NT, 2) void b_adjoint_kernel(const bf16_t* __restrict__ G, int64_t ldn,
                                                             const bf16_t* __restrict__ Pt, const int32_t* __restrict__ c,
@@ -526,7 +529,7 @@ __global__ __launch_bounds__(E::NT, 2) void b_adjoint_kernel(const bf16_t* __res
 #pragma unroll
   for (int j = 0; j < E::FN; ++j) limit[j] = bound[E::wn() + 16 * j + (lane & 15)];
   const typename E::Op oa{G, ldn, m0, B}, ob{Pt, ldn, n0, h};
-  const int kbeg = first / 32 * 32;
+  const int kbeg = E::MASK == B_ALL ? first / 64 * 64 : first / 32 * 32;
   const typename E::Lanes L = E::start(oa, ob, kbeg, ldn, st);
   floatx4_t acc[E::FM][E::FN];
   E::run(oa, ob, L, {kbeg, n, first, last}, limit, st, acc);
@@ -640,29 +643,41 @@ using BHidden = BE<64, 64, 2, 2, 4, true, B_BELOW>;
 using BOut = BE<64, 128, 2, 4, 2, false, B_BELOW>;
 using BAdjoint = BE<64, 64, 2, 2, 4, false, B_FROM>;
 using BAdjointLarge = BE<128, 128, 2, 4, 2, false, B_FROM>;
+using BAdjointPm = BE<64, 64, 2, 2, 4, false, B_ALL>;
+using BAdjointLargePm = BE<128, 128, 2, 4, 2, false, B_ALL>;
 using BWeight = BE<128, 128, 4, 4, 4, false, B_ALL>;
 using BWeightSmall = BE<64, 64, 2, 2, 4, false, B_ALL>;
 
 static int64_t b_tiles(int64_t x, int t) { return (x + t - 1) / t; }
 
 template <class E>
-static hipError_t b_adjoint_t(const vqmc_made& m, int64_t B, const bf16_t* G, const bf16_t* Rt, bf16_t* Dt, float* db1_part,
-                              int* np1, hipStream_t st) {
+static hipError_t b_adjoint_t(const vqmc_made& m, const bf16_t* Pt, int64_t B, const bf16_t* G, const bf16_t* Rt, bf16_t* Dt,
+                              float* db1_part, int* np1, hipStream_t st) {
   const int64_t ldn = round_up(m.n, kPad), ldh = round_up(m.h, kPad), ldB = round_up(B, kPad);
   *np1 = (int)b_tiles(B, E::BM);
-  b_adjoint_kernel<E><<<b_grid(*np1, b_tiles(m.h, E::BN)), E::NT, 0, st>>>(G, ldn, (const bf16_t*)m.Pt, m.c, m.n, m.h, B, Rt,
-                                                                           Dt, ldB, db1_part, ldh);
+  b_adjoint_kernel<E><<<b_grid(*np1, b_tiles(m.h, E::BN)), E::NT, 0, st>>>(G, ldn, Pt, m.c, m.n, m.h, B, Rt, Dt, ldB, db1_part,
+                                                                           ldh);
   return hipGetLastError();
 }
 
-hipError_t launch_b_adjoint(const vqmc_made& m, int64_t B, const bf16_t* G, const bf16_t* Rt, bf16_t* Dt,
+hipError_t launch_b_adjoint(const vqmc_made& m, bool tables, int64_t B, const bf16_t* G, const bf16_t* Rt, bf16_t* Dt,
                             float* db1_part, int* np1, hipStream_t st) {
   // 128 x 128 tiles once there are two per CU (the ranges of a column of tiles differ up to its whole
   // length; fewer large tiles leave CUs with one short run): 53 against 63 us at 512 of them (n = h = 2000,
   // B = 4096), 33.5 against 31.6 at 256 (h = 1000), 150 against 56 at n = 10000, h = 1000, B = 2048
   const bool large = b_tiles(B, 128) * b_tiles(m.h, 128) >= 512;
-  return large ? b_adjoint_t<BAdjointLarge>(m, B, G, Rt, Dt, db1_part, np1, st)
-               : b_adjoint_t<BAdjoint>(m, B, G, Rt, Dt, db1_part, np1, st);
+  // The masked copy of P^T among the sampler's tables spares the masks, which are most of a stage where a tile's units lie
+  // far apart (n = 10000, h = 100, B = 2048: 42 against 77 us; h = 1000 alike, n = h = 2000: 25 against 31)
+  if (tables && m.band && ((uintptr_t)m.band & 15) == 0) {
+    int64_t z, u, pm;
+    int nz, nu;
+    sample_tables_layout(m.n, m.h, m.wdtype, &z, &u, &pm, &nz, &nu);
+    const bf16_t* Pm = (const bf16_t*)((const uint8_t*)m.band + pm);
+    return large ? b_adjoint_t<BAdjointLargePm>(m, Pm, B, G, Rt, Dt, db1_part, np1, st)
+                 : b_adjoint_t<BAdjointPm>(m, Pm, B, G, Rt, Dt, db1_part, np1, st);
+  }
+  return large ? b_adjoint_t<BAdjointLarge>(m, (const bf16_t*)m.Pt, B, G, Rt, Dt, db1_part, np1, st)
+               : b_adjoint_t<BAdjoint>(m, (const bf16_t*)m.Pt, B, G, Rt, Dt, db1_part, np1, st);
 }
 
 template <class E>

@@ -113,7 +113,8 @@ hipError_t launch_b_logp(const vqmc_made& m, const int8_t* S, int64_t B, const u
                          float* Z /* nullable */, int* nparts, hipStream_t st);
 hipError_t launch_b_out_grad(const vqmc_made& m, const int8_t* S, int64_t B, const uint16_t* R, const float* coef,
                              uint16_t* G, uint16_t* Gt, uint16_t* St, float* db2_part, int* np2, hipStream_t st);
-hipError_t launch_b_adjoint(const vqmc_made& m, int64_t B, const uint16_t* G, const uint16_t* Rt, uint16_t* Dt,
+// (tables: from the masked copy in m.band, if m.band is set)
+hipError_t launch_b_adjoint(const vqmc_made& m, bool tables, int64_t B, const uint16_t* G, const uint16_t* Rt, uint16_t* Dt,
                             float* db1_part, int* np1, hipStream_t st);
 // dP, and db1, db2 from their partial sums
 hipError_t launch_b_weight(const vqmc_made& m, int64_t B, const uint16_t* Gt, const uint16_t* St, const uint16_t* Rt,
