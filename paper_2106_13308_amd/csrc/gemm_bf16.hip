@@ -593,13 +593,16 @@ __device__ inline void b_weight_tile(const bf16_t* Gt, const bf16_t* Rt, const b
 }
 
 // dP[d][k] = sum_b Gt[d][b] Rt[k][b] (k < c[d]), sum_b St[d][b] Dt[k][b] (else): a workgroup per tile, for the lower
-// half if it has an element of it, else for the upper one; nextra more per row of tiles for the upper halves of those
-// crossed by the staircase.  The first nbias workgroups sum the partials of the bias gradients instead.
+// half if it has an element of it, else for the upper one.  The upper halves of the tiles that the staircase crosses have
+// workgroups of their own: one per row of tiles, beside the row's, for the first such tile, and one per column for the
+// row that comes into the column further on.  (So any staircase has one workgroup a half: all degrees equal, n = h = 2000,
+// B = 2048: 36 us; with the later tiles of a row in one workgroup 230.)  lead: of the columns, rounded up to eight.  The first nbias
+// workgroups sum the partials of the bias gradients instead.
 template <class E>
 __global__ __launch_bounds__(E::NT, 2) void b_weight_kernel(const bf16_t* __restrict__ Gt, const bf16_t* __restrict__ Rt,
                                                            const bf16_t* __restrict__ St, const bf16_t* __restrict__ Dt,
                                                            int64_t ldB, const int32_t* __restrict__ c, int n, int h,
-                                                           float* __restrict__ dP, int nbias, int nextra,
+                                                           float* __restrict__ dP, int nbias, int lead,
                                                            const float* __restrict__ db1_part, int np1, int64_t ldh,
                                                            const float* __restrict__ db2_part, int np2, int64_t ldn,
                                                            float* __restrict__ db1, float* __restrict__ db2) {
@@ -624,18 +627,38 @@ __global__ __launch_bounds__(E::NT, 2) void b_weight_kernel(const bf16_t* __rest
     return;
   }
   const int nrow = (n + E::BM - 1) / E::BM, ncol = (h + E::BN - 1) / E::BN;
-  const int w = (int)blockIdx.x - nbias, wq = __builtin_amdgcn_readfirstlane((w >> 3) / (ncol + nextra));
-  const int row = (w & 7) + 8 * wq, q = (w >> 3) - (ncol + nextra) * wq - nextra;
-  if (row >= nrow) return;
-  const int d0 = row * E::BM;
-  const int cfirst = __builtin_amdgcn_readfirstlane(c[d0]), clast = __builtin_amdgcn_readfirstlane(c[min(d0 + E::BM, n) - 1]);
-  int col = q >= 0 ? q : cfirst / E::BN + nextra + q;
-  const bool upper = q < 0 || q * E::BN >= clast;
-  const int end = q >= 0 ? (q + 1) * E::BN : min(clast, h);
-  for (; col * E::BN < end; col += nextra) {
-    if (min(col * E::BN + E::BN, h) <= cfirst && q < 0) continue;
-    b_weight_tile<E>(Gt, Rt, St, Dt, ldB, c, n, h, dP, d0, col * E::BN, upper, st);
+  int row, col;
+  bool upper;
+  const int w = (int)blockIdx.x - nbias, v = max(w - lead, 0);
+  const int g = __builtin_amdgcn_readfirstlane(v / (8 * (ncol + 1))), i = v - 8 * (ncol + 1) * g;
+  if (w < lead) {
+    // the row in which the staircase comes into column w: the first whose lower elements reach it
+    col = w;
+    row = 0;
+    for (int r0 = 0;; r0 += 64) {
+      const int r = r0 + lane;
+      const int k = __popcll(__ballot(r < nrow && c[min((r + 1) * E::BM, n) - 1] <= col * E::BN));
+      row += k;
+      if (k < 64) break;
+    }
+    row = __builtin_amdgcn_readfirstlane(row);
+    // (the row's own workgroup has its first column)
+    if (col >= ncol || row >= nrow || c[row * E::BM] / E::BN >= col) return;
+    upper = true;
+  } else if (i < 8) {
+    row = i + 8 * g;
+    if (row >= nrow) return;
+    const int cfirst = __builtin_amdgcn_readfirstlane(c[row * E::BM]);
+    col = cfirst / E::BN;
+    if (cfirst >= h || col * E::BN >= __builtin_amdgcn_readfirstlane(c[min((row + 1) * E::BM, n) - 1])) return;
+    upper = true;
+  } else {
+    row = (i & 7) + 8 * g;
+    if (row >= nrow) return;
+    col = (i >> 3) - 1;
+    upper = col * E::BN >= __builtin_amdgcn_readfirstlane(c[min((row + 1) * E::BM, n) - 1]);
   }
+  b_weight_tile<E>(Gt, Rt, St, Dt, ldB, c, n, h, dP, row * E::BM, col * E::BN, upper, st);
 }
 
 // ---------------------------------------------------------------- launches
@@ -687,12 +710,9 @@ static hipError_t b_weight_t(const vqmc_made& m, int64_t B, const bf16_t* Gt, co
   const int64_t ldn = round_up(m.n, kPad), ldh = round_up(m.h, kPad), ldB = round_up(B, kPad);
   const int nbias = (int)(round_up((int64_t)m.n + m.h, 512) / 64);  // a multiple of 8: the tiles keep their XCDs
   const int64_t nrow = b_tiles(m.n, E::BM), ncol = b_tiles(m.h, E::BN);
-  // tiles of a row that a regular staircase crosses; one more where there are CUs to spare for the rows in
-  // which it passes from one column to the next (17.7 against 30 us at n = 3001, h = 611, B = 1500; with many
-  // tiles the idle workgroups cost more: 70 against 85 us at n = 10000, h = 1000, B = 2048)
-  const int nextra = (int)((ncol + nrow - 1) / nrow + (nrow * (ncol + 2) <= 256));
-  b_weight_kernel<E><<<nbias + b_grid(nrow, ncol + nextra), E::NT, 0, st>>>(
-      Gt, Rt, St, Dt, ldB, m.c, m.n, m.h, dP, nbias, nextra, db1_part, np1, ldh, db2_part, np2, ldn, db1, db2);
+  const int lead = (int)round_up(ncol, 8);
+  b_weight_kernel<E><<<nbias + lead + b_grid(nrow, ncol + 1), E::NT, 0, st>>>(
+      Gt, Rt, St, Dt, ldB, m.c, m.n, m.h, dP, nbias, lead, db1_part, np1, ldh, db2_part, np2, ldn, db1, db2);
   return hipGetLastError();
 }
 
