@@ -22,8 +22,9 @@
 // (BK = 16).  Accumulation is always FP32.  Intermediates that a later product contracts over the batch
 // (R, G, S, D) are written batch-contiguous (transposed) by the producing epilogue, which the MFMA
 // accumulator layout makes a 4-element store.  Log p, its gradient and the SR factors run in gemm_f32.hip
-// and gemm_bf16.hip instead: here are left the plain sampler and the FP32 TIM forward pass, whose draws and
-// FP64 energies stay what they are to the last bit, and the forward-mode product.
+// and gemm_bf16.hip; this engine has the plain sampler and the FP32 TIM forward pass, whose draws and
+// FP64 energies stay what they are to the last bit, the forward-mode product, log pi of few sites and many samples, and BF16
+// inputs that are not 16-byte aligned.
 #include <algorithm>
 
 #include "common.hpp"
