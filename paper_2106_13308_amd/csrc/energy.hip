@@ -145,10 +145,10 @@ __global__ __launch_bounds__(EB_THREADS, 8) void energy_csr_bits_kernel(int n, i
 // No edge needs its row's sum, so L lanes share a row with nothing to add up between
 // them (L from the mean row length: a lane gets 8 to 16 edges of a row, or one lane a whole row), and the
 // bytes run on across rows; they are added to 64-bit sums before the weights in them exceed 255.
-// A step of a lane (sixteen edges) whose weights do not fit so - negative ones, or a sum above 255 - adds in
-// 16-bit halves, two samples a word, while |w| < 2047; larger weights go to the 64-bit sums directly.  (130, 300 and 820
-// vector instructions a step.  Weights +-1: 32 us at n = 10000, degree 10, B = 2048, 52 by the 64-bit sums, 58 by a
-// thread per row; mean weight 33 alike, 27, 37 and 55 us.)
+// A step of a lane (sixteen edges) whose weights do not fit so - negative ones, or a sum above 255 - adds its edges to
+// those sums directly, a 64-bit multiply-add by 0 or 1 per sample (selects and adds with carry took five instructions:
+// weights +-1 at n = 10000, degree 10, B = 2048 52 us, 32 so, 58 by a thread per row; one vertex with 9999 edges of
+// large weights 5.9 ms, 2.3 so and 2.3 by a thread).
 //
 // What bounds it: the address coalescing of the rows' loads (16 cycles a load instruction when the lanes lie
 // apart), then their latency.  So a lane takes four edges by one 16-byte load of each array, and
@@ -156,7 +156,6 @@ __global__ __launch_bounds__(EB_THREADS, 8) void energy_csr_bits_kernel(int n, i
 // edges a step, 64-bit sums per row): n = 500, 75 % of the edges, B = 1024: 35 -> 18; n = 10000, degree 10, B = 2048:
 // 41 -> 30.
 constexpr int EC_U = 4;
-typedef __attribute__((ext_vector_type(2))) short s16x2_t;
 template <bool RP_LDS, int EC_RB>
 __global__ __launch_bounds__(EB_THREADS, EC_RB == 2 ? 8 : 4) void energy_csr_bytes_kernel(int n, int64_t lds,
                                                                      const int64_t* __restrict__ rowptr,
@@ -207,27 +206,6 @@ __global__ __launch_bounds__(EB_THREADS, EC_RB == 2 ? 8 : 4) void energy_csr_byt
 #pragma unroll
     for (int q = 0; q < EMSE; ++q) y[q] += ((q < 4 ? ylo : yhi) >> (8 * (q & 3))) & 0xFFu;
     ylo = yhi = held = 0u;
-  };
-  uint32_t z[EMSE / 2], held16 = 0u;  // Y_2p and Y_2p+1 in the halves of z[p], and a bound of the |weights| in them
-#pragma unroll
-  for (int p = 0; p < EMSE / 2; ++p) z[p] = 0u;
-  auto flush16 = [&]() {
-#pragma unroll
-    for (int p = 0; p < EMSE / 2; ++p) {
-      y[2 * p] += (int16_t)z[p];
-      y[2 * p + 1] += (int32_t)z[p] >> 16;
-      z[p] = 0u;
-    }
-    held16 = 0u;
-  };
-  // the bits that any |w| of a step has, give or take one: |w| <= mag + 1
-  auto magnitude = [](const uint32_t(&wt)[EC_RB][EC_U]) {
-    uint32_t mag = 0u;
-#pragma unroll
-    for (int r = 0; r < EC_RB; ++r)
-#pragma unroll
-      for (int u = 0; u < EC_U; ++u) mag |= wt[r][u] ^ (uint32_t)((int32_t)wt[r][u] >> 31);
-    return mag;
   };
   const int groups = EB_THREADS / lanes, sub = t & (lanes - 1);
   const __amdgpu_buffer_rsrc_t rcol = __builtin_amdgcn_make_buffer_rsrc((void*)col, 0, (int)(uint32_t)(4 * nnz), 0x00020000);
@@ -280,34 +258,18 @@ __global__ __launch_bounds__(EB_THREADS, EC_RB == 2 ? 8 : 4) void energy_csr_byt
             ylo += w4 & (si[r].x ^ sj.x);
             yhi += w4 & (si[r].y ^ sj.y);
           }
-      } else if (uint32_t mag = magnitude(wt); mag <= 32767u / (EC_RB * EC_U) - 1u) {
-        const uint32_t more = EC_RB * EC_U * (mag + 1u);
-        if (held16 + more > 32767u) flush16();
-        held16 += more;
-        wsum += (int32_t)sum;
-#pragma unroll
-        for (int r = 0; r < EC_RB; ++r)
-#pragma unroll
-          for (int u = 0; u < EC_U; ++u) {
-            const uint2 sj = sw[j[r][u]];
-            const uint32_t dx = si[r].x ^ sj.x, dy = si[r].y ^ sj.y, w2 = __builtin_amdgcn_perm(0u, wt[r][u], 0x01000100u);
-#pragma unroll
-            for (int p = 0; p < EMSE / 2; ++p) {
-              const uint32_t m = __builtin_amdgcn_perm(0u, p < 2 ? dx : dy, p & 1 ? 0x03030202u : 0x01010000u);
-              z[p] = __builtin_bit_cast(uint32_t, __builtin_bit_cast(s16x2_t, z[p]) + __builtin_bit_cast(s16x2_t, w2 & m));
-            }
-          }
       } else {
 #pragma unroll
         for (int r = 0; r < EC_RB; ++r)
 #pragma unroll
           for (int u = 0; u < EC_U; ++u) {
+            if (wt[r][u] == 0u) continue;
             const uint2 sj = sw[j[r][u]];
             const uint32_t dx = si[r].x ^ sj.x, dy = si[r].y ^ sj.y;
             const int64_t we = (int32_t)wt[r][u];
             wsum += we;
 #pragma unroll
-            for (int q = 0; q < EMSE; ++q) y[q] += (((q < 4 ? dx : dy) >> (8 * (q & 3))) & 1u) ? we : 0;
+            for (int q = 0; q < EMSE; ++q) y[q] += we * (int32_t)(((q < 4 ? dx : dy) >> (8 * (q & 3))) & 1u);  // one multiply-add
           }
       }
 #pragma unroll
@@ -315,7 +277,6 @@ __global__ __launch_bounds__(EB_THREADS, EC_RB == 2 ? 8 : 4) void energy_csr_byt
     }
   }
   flush();
-  flush16();
   // E_q of the lane, then the sums over the wave: three exchanges that halve the samples a lane holds,
   // three over the eight lanes with the same sample, then the sixteen waves in order
 #pragma unroll

@@ -1,18 +1,18 @@
-"""The sparse integer energies at the edges of their 16-bit sums, in both forms of the kernel (four rows at a time, or
-two with two workgroups a CU: batches past 2048), against the exact oracle."""
+"""The sparse integer energies for weights that do not fit the byte lanes, in both forms of the kernel (four rows at a
+time, or two with two workgroups a CU: batches past 2048), against the exact oracle."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-# the largest weights a step of sixteen (eight) edges takes in halves, one more, both signs, mixed with small ones
-WEIGHTS = [(-1, 1), (2046, -2047), (2047, -2048), (4094, -4095), (4095, -4096), (40, 1), (255, 0), (32767, -32768), (2046, 1), (-1, 70000)]
+# both signs, a byte and more, 16 bits and more, next to weights that do fit
+WEIGHTS = [(-1, 1), (2046, -2047), (16, 15), (40, 1), (255, 0), (256, 1), (32767, -32768), (-1, 70000), (2**31 - 1, -2**31)]
 
 
 @pytest.mark.parametrize("n,B", [(130, 9), (150, 2051), (2300, 2049)])
 @pytest.mark.parametrize("w", WEIGHTS)
-def test_csr_halves(n, B, w):
+def test_csr_weights(n, B, w):
     """All pairs (n = 2300: a path with chords), weights of the two values at random or the first alone; strings at random,
     alternating (half of all pairs of unequal spins) and all equal."""
     from oracle import energy as oen
