@@ -781,7 +781,7 @@ static bool staged_logp_bf16(const Geom& g) { return g.n <= 64 && g.h <= 64; }
 // where the FP32 products have just turned to their large tiles (64 < h <= 128) and for fewer samples.
 static bool staged_f32(const Geom& g) {
   if (g.n <= 64 && g.B >= 16384 && (g.B >= 32768 || g.h <= 64 || g.h > 128)) return true;
-  return g.B >= 65536 && (g.n <= 320 ? g.n <= 128 || g.h <= 256 : g.h <= 64);
+  return g.B >= 40000 && (g.n <= 384 ? g.n <= 128 || g.h <= 256 : g.h <= 64);
 }
 
 template <typename T>

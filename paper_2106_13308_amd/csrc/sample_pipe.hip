@@ -262,7 +262,7 @@ __global__ __launch_bounds__(SP_THREADS, sizeof(WT) == 2 && !PLANES ? 3 : 4) voi
         v[e] = (inside || d + e < n) ? -lg * SP_SCALE : 0.f;
       }
     };
-    if (PLANES && SP_T * (blk + 1) <= n) draw(true);
+    if ((PLANES || sizeof(WT) == 4) && SP_T * (blk + 1) <= n) draw(true);
     else if (d < n) draw(false);
     *(float4*)(dst + s * SP_T + 4 * q4) = make_float4(v[0], v[1], v[2], v[3]);
   };
