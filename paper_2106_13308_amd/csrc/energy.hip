@@ -717,7 +717,7 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
       const bool rpl = swb + rpb + redb <= 160 * 1024;
       const size_t sb = swb + (rpl ? rpb : 0) + redb;
       // two workgroups a CU where there is work and LDS for them, two rows at a time then (64 registers): n = 500, 8 % of the
-      // edges, B = 16384: 42 against 74 us; one workgroup a CU: four rows, 17 against 29 us at n = 16000, degree 6, B = 1
+      // edges, B = 16384: 35 against 74 us; one workgroup a CU: four rows, 17 against 29 us at n = 16000, degree 6, B = 1
       const bool pair = grid > 256 && 2 * sb <= 160 * 1024;
       auto kern = pair ? (rpl ? energy_csr_bytes_kernel<true, 2> : energy_csr_bytes_kernel<false, 2>)
                        : (rpl ? energy_csr_bytes_kernel<true, 4> : energy_csr_bytes_kernel<false, 4>);

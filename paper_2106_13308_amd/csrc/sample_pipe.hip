@@ -250,7 +250,7 @@ __global__ __launch_bounds__(SP_THREADS, sizeof(WT) == 2 && !PLANES ? 3 : 4) voi
     const int d = SP_T * blk + 4 * q4;
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     // inside: every site of the block exists, so no selects (all blocks but the last; with few units a block these draws are
-    // its longest helper work: n = 10000, h = 100, BF16: 230 us, 240 with them; without planes no gain)
+    // its longest helper work: n = 10000, h = 100, BF16: 230 us, 240 with them; BF16 without planes: no gain)
     auto draw = [&](bool inside) {
       const float4 u4 = site_uniforms(seed, step, tag, (uint64_t)(b0 + s + offset), (uint32_t)(d >> 2));
       const float uv[4] = {u4.x, u4.y, u4.z, u4.w};
