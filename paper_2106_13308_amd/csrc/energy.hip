@@ -22,12 +22,14 @@ namespace vqmc {
 // accumulated exactly in int64 (integer weights) or in double (float weights, whose sums
 // of exact terms only differ from the oracle's by summation order).  A fixed thread -> row
 // map and fixed-shape reductions make the result deterministic.
-// SHARED: several lanes a row; without it the row loop is that of one lane.  64 registers, so that two workgroups share
-// a CU (float weights, degree 20, n = 3000, B = 16384: 152 against 219 us with 66; mean row 3, n = 1000: 43 against 66).
+// SHARED: several lanes a row; without it the row loop is that of one lane.  WAVES = 8: 64 registers, so that two workgroups
+// share a CU (float weights, degree 20, n = 3000, B = 16384: 152 against 219 us with 66; mean row 3, n = 1000: 43 against 66).
+// Shared float rows spill two registers so; with no more workgroups than CUs they take WAVES = 4 (n = 1973, 25 % of the edges,
+// B = 271, with the sampler: 310 against 316 us).
 constexpr int EMSE = 8;
 constexpr int EB_THREADS = 1024;
-template <typename WT, typename AT, bool RP_LDS, bool SHARED>
-__global__ __launch_bounds__(EB_THREADS, 8) void energy_csr_bits_kernel(int n, int64_t lds,
+template <typename WT, typename AT, bool RP_LDS, bool SHARED, int WAVES = 8>
+__global__ __launch_bounds__(EB_THREADS, WAVES) void energy_csr_bits_kernel(int n, int64_t lds,
                                                                     const int64_t* __restrict__ rowptr,
                                                                     const int32_t* __restrict__ col,
                                                                     const WT* __restrict__ w,
@@ -732,7 +734,9 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
                           : (rp_lds ? energy_csr_bits_kernel<int32_t, int64_t, true, false> : energy_csr_bits_kernel<int32_t, int64_t, false, false>);
     go(kern, (const int32_t*)H.w, (int64_t*)E);
   } else {
-    auto kern = lanes > 1 ? (rp_lds ? energy_csr_bits_kernel<float, double, true, true> : energy_csr_bits_kernel<float, double, false, true>)
+    const bool pair = grid > 256;  // more workgroups than CUs
+    auto kern = lanes > 1 ? (pair ? (rp_lds ? energy_csr_bits_kernel<float, double, true, true> : energy_csr_bits_kernel<float, double, false, true>)
+                                  : (rp_lds ? energy_csr_bits_kernel<float, double, true, true, 4> : energy_csr_bits_kernel<float, double, false, true, 4>))
                           : (rp_lds ? energy_csr_bits_kernel<float, double, true, false> : energy_csr_bits_kernel<float, double, false, false>);
     go(kern, (const float*)H.w, (double*)E);
   }
