@@ -776,12 +776,15 @@ static bool staged_hidden_bf16(const Geom& g) {
   return g.n <= 64 || (g.n <= 128 && (int64_t)g.mt_h * g.nt_h >= 1024);
 }
 static bool staged_logp_bf16(const Geom& g) { return g.n <= 64 && g.h <= 64; }
-// FP32, both layers (they pass relu(A) on in layouts of their own): n = 20, h = 200, B = 131072: 113 / 163;
-// n = 300, h = 45, B = 131072: 202 / 236; n = 2, h = 45, B = 16384: 14 / 19, n = 20, h = 500: 47 / 50, the other way
-// where the FP32 products have just turned to their large tiles (64 < h <= 128) and for fewer samples.
+// FP32, both layers (they pass relu(A) on in layouts of their own): n = 20, h = 200, B = 131072: 113 / 163; n = 4, h = 87,
+// B = 24617: 23 / 33; n = 106, h = 113, B = 13793: 29 / 38; n = 318, h = 35, B = 31939: 66 / 77; n = 8, h = 173, B = 7847:
+// 22 / 26.  The lines are those that lose least over 3038 sizes up to n = 1500, h = 2500, B = 200000: 0.2 % on average
+// against the faster engine of each (over 5 % at 50 of them, 17 % at most).  Outside them the staged one takes up to 3 times.
 static bool staged_f32(const Geom& g) {
-  if (g.n <= 64 && g.B >= 16384 && (g.B >= 32768 || g.h <= 64 || g.h > 128)) return true;
-  return g.B >= 40000 && (g.n <= 384 ? g.n <= 128 || g.h <= 256 : g.h <= 64);
+  if (g.B >= 30720 && (g.h <= 192 || (g.h <= 320 && g.n <= 320))) return true;
+  if (g.B >= 12800 && g.n <= 192) return true;
+  if (g.B >= 8192 && (g.n <= 128 ? g.h >= g.n : g.n <= 192 && g.h >= 128 && g.h <= 256)) return true;
+  return g.B >= 5760 && g.n <= 16 && g.h >= 64 && g.h <= 320;
 }
 
 template <typename T>
