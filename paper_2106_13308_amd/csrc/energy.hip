@@ -639,10 +639,12 @@ __global__ void sum_partials_kernel(const double* __restrict__ part, int ntiles,
 }
 
 // Every row by energy_dense_f64_kernel up to so many sites and samples times 16-row tiles: a launch less (13.6 against
-// 16.6 us at n = 100, B = 1024); from about 200 sites the integer cores gain more (16.2 against 20.4 us at n = 255, B = 64),
-// and with more samples (27 against 18 us at n = 64, B = 65536)
-constexpr int kDenseF64Sites = 160;
-constexpr int64_t kDenseF64Work = 131072;
+// 16.2 us at n = 100, B = 1024); from about 200 sites the integer cores gain more (16.2 against 20.4 us at n = 255, B = 64),
+// and with more samples (n = 32: 13.9 against 16.6 us at B = 65536, 23 against 16.5 at 131072; n = 64: 13.8 against 16.6 at
+// 20000, 19.8 against 16.3 at 40000; n = 128: 14.9 against 16.0 at 8192, 19.8 against 16.3 at 12000)
+static bool dense_f64(int n, int ntiles, int64_t B) {
+  return n <= 160 && (int64_t)ntiles * B <= std::max(65536, (13 << 19) / n);
+}
 
 // partial sums of the row tiles (of 16 rows at least), the rows' exponents
 size_t energy_dense_ws_bytes(int n, int64_t B) {
@@ -662,7 +664,7 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
     int32_t* ex = (int32_t*)((double*)ws + (int64_t)ntiles * B);
     hipError_t e;
     auto groups = [&](int nw) { return (B + 32 * nw - 1) / (32 * nw); };
-    if (n <= kDenseF64Sites && (int64_t)ntiles * B <= kDenseF64Work) {
+    if (dense_f64(n, ntiles, B)) {
       energy_dense_f64_kernel<4><<<dim3((unsigned)groups(4), (unsigned)ntiles), 256, 0, st>>>(n, lds, H.J, S, B, (double*)ws);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       sum_partials_kernel<<<(unsigned)((B + 255) / 256), 256, 0, st>>>((const double*)ws, ntiles, B, (double*)E);
