@@ -737,6 +737,10 @@ hipError_t launch_energy(const vqmc_hamiltonian& H, const int8_t* S, int64_t B, 
     go(kern, (const int32_t*)H.w, (int64_t*)E);
   } else {
     const bool pair = grid > 256;  // more workgroups than CUs
+    // one lane a row up to 32 edges a row where there are rows for most of the threads and a CU has one workgroup
+    // (n = 1421, mean row 26, B = 2: 26.6 against 29.2 us with two lanes; n = 638 17.5 against 16.7; two workgroups a CU,
+    // n = 3400, mean row 25, B = 4017: 163 against 117)
+    if (!pair && n >= 768 && H.nnz < (int64_t)32 * n) lanes = 1;
     auto kern = lanes > 1 ? (pair ? (rp_lds ? energy_csr_bits_kernel<float, double, true, true> : energy_csr_bits_kernel<float, double, false, true>)
                                   : (rp_lds ? energy_csr_bits_kernel<float, double, true, true, 4> : energy_csr_bits_kernel<float, double, false, true, 4>))
                           : (rp_lds ? energy_csr_bits_kernel<float, double, true, false> : energy_csr_bits_kernel<float, double, false, false>);
